@@ -152,7 +152,8 @@ hipError_t ensure_twiddles(int device) {
   std::lock_guard<std::mutex> lk(g_tw_mutex);
   if ((int)g_tw_done.size() <= device) g_tw_done.resize(device + 1, 0);
   if (g_tw_done[device]) return hipSuccess;
-  hipError_t e = upload_twiddles(device);
+  hipError_t e = upload_twiddles();
+  if (e == hipSuccess) e = upload_twiddles_rows();
   if (e == hipSuccess) g_tw_done[device] = 1;
   return e;
 }
@@ -591,13 +592,12 @@ s2w_status s2w_get_tuning(const s2w_plan* p, s2w_tuning* t) {
   return S2W_OK;
 }
 
-// Half-precision setup: per staging pass of rs rows, transform to float32 spectra in the
-// workspace, then quantize with one power-of-two scale per (grid row, bin).
+// Half-precision setup: spectra as half words with one power-of-two scale per (grid row, bin),
+// the rows' maxima kept in the workspace meanwhile.
 static s2w_status set_operators_half(s2w_plan* p, const float* G_chunk, const float* F_chunk, int64_t row0,
                                      int64_t nrows, hipStream_t st) {
   const Geometry& g = p->geo;
   const HalfGeo& h = p->hg;
-  float2* stg = (float2*)(p->ws + p->lay.staging);
   uint32_t* Gq = (uint32_t*)(p->op + p->lay.gq);
   uint32_t* Fq = (uint32_t*)(p->op + p->lay.fq);
   float* sG = (float*)(p->op + p->lay.sg);
@@ -608,20 +608,14 @@ static s2w_status set_operators_half(s2w_plan* p, const float* G_chunk, const fl
     if (e != hipSuccess) return hip_fail(p, e, "set_operators: clear padding");
     p->pad_zeroed = true;
   }
-  for (int64_t r = 0; r < nrows; r += h.rs) {
-    const int64_t n = std::min<int64_t>(h.rs, nrows - r);
-    e = launch_rfft_rows(G_chunk + r * g.nsub * g.nt, n, g.nsub, h.nsq, stg, (int64_t)g.M * h.nsq, 1, h.nsq, g, 1.0f,
-                         st);
-    if (e == hipSuccess)
-      e = launch_quant_rows(h.ht_g, stg, n, g.M, g.nsub, h.nsq, Gq, row0 + r, 0, 0, 0, sG, h.ngq / 16, st);
-    if (e != hipSuccess) return hip_fail(p, e, "set_operators: elastic transform/quantize");
-    e = launch_rfft_rows(F_chunk + r * g.nobs * g.nt, n, g.nobs, h.noq, stg, (int64_t)g.M * h.noq, 1, h.noq, g, 1.0f,
-                         st);
-    if (e == hipSuccess)
-      e = launch_quant_rows(h.ht_f, stg, n, g.M, g.nobs, h.noq, Fq, row0 + r, 1, (int64_t)h.noq * h.ngq, h.ngq, sF,
-                            0, st);
-    if (e != hipSuccess) return hip_fail(p, e, "set_operators: acoustic transform/quantize");
-  }
+  uint32_t* mx = (uint32_t*)(p->ws + p->lay.staging);
+  const int64_t mx_words = 2 * (int64_t)h.rs * g.M * std::max(h.nsq, h.noq);
+  e = launch_quant_spectra(h.ht_g, true, G_chunk, nrows, g.nsub, h.nsq, Gq, row0, 0, 0, h.ngq / 16, sG, mx, mx_words, g,
+                           st);
+  if (e != hipSuccess) return hip_fail(p, e, "set_operators: elastic transform/quantize");
+  e = launch_quant_spectra(h.ht_f, false, F_chunk, nrows, g.nobs, h.noq, Fq, row0, h.ngq, (int64_t)h.noq * h.ngq, 0,
+                           sF, mx, mx_words, g, st);
+  if (e != hipSuccess) return hip_fail(p, e, "set_operators: acoustic transform/quantize");
   return S2W_OK;
 }
 
@@ -641,10 +635,12 @@ static s2w_status set_operators_b32(s2w_plan* p, const float* G_chunk, const flo
     if (e != hipSuccess) return hip_fail(p, e, "set_operators: clear padding");
     p->pad_zeroed = true;
   }
-  e = launch_rfft_rows(G_chunk, nrows, g.nsub, f.nsk, Gs + row0 * g.M * f.nsk, (int64_t)g.M * f.nsk, 1, f.nsk, g,
-                       1.0f, st);
+  const int64_t gin = (int64_t)g.nsub * g.nt, fin = (int64_t)g.nobs * g.nt;
+  e = launch_rfft_units(G_chunk, gin, g.nt, (int)nrows, (int)nrows, g.nsub, f.nsk, Gs + row0 * g.M * f.nsk,
+                        (int64_t)g.M * f.nsk, 1, f.nsk, g, 1.0f, st);
   if (e != hipSuccess) return hip_fail(p, e, "set_operators: elastic transform");
-  e = launch_rfft_rows(F_chunk, nrows, g.nobs, f.nok, Fs + row0, 1, f.ngk, (int64_t)f.nok * f.ngk, g, 1.0f, st);
+  e = launch_rfft_units(F_chunk, g.nt, fin, g.nobs, f.nok, (int)nrows, (int)nrows, Fs + row0, f.ngk, 1,
+                        (int64_t)f.nok * f.ngk, g, 1.0f, st);
   if (e != hipSuccess) return hip_fail(p, e, "set_operators: acoustic transform");
   return S2W_OK;
 }
@@ -693,11 +689,11 @@ s2w_status s2w_set_operators(s2w_plan* p, const float* G_chunk, const float* F_c
   float2* Gh = (float2*)(p->op + p->lay.gh);
   float2* Fh = (float2*)(p->op + p->lay.fh);
   // spectra of row (g, column c) land at [g][c][0..M)
-  hipError_t e = launch_rfft_rows(G_chunk, nrows, g.nsub, g.nsp, Gh + row0 * g.M * g.nsp, (int64_t)g.M * g.nsp, g.M,
-                                  1, g, 1.0f, st);
+  hipError_t e = launch_rfft_units(G_chunk, (int64_t)g.nsub * g.nt, g.nt, (int)nrows, (int)nrows, g.nsub, g.nsp,
+                                   Gh + row0 * g.M * g.nsp, (int64_t)g.M * g.nsp, g.M, 1, g, 1.0f, st);
   if (e != hipSuccess) return hip_fail(p, e, "set_operators: elastic transform");
-  e = launch_rfft_rows(F_chunk, nrows, g.nobs, g.nop, Fh + row0 * g.M * g.nop, (int64_t)g.M * g.nop, g.M, 1, g,
-                       1.0f, st);
+  e = launch_rfft_units(F_chunk, (int64_t)g.nobs * g.nt, g.nt, (int)nrows, (int)nrows, g.nobs, g.nop,
+                        Fh + row0 * g.M * g.nop, (int64_t)g.M * g.nop, g.M, 1, g, 1.0f, st);
   if (e != hipSuccess) return hip_fail(p, e, "set_operators: acoustic transform");
   for (int64_t r = row0; r < row0 + nrows; ++r) {
     if (!p->row_set[(size_t)r]) {
@@ -727,25 +723,42 @@ static int64_t part_floats(const s2w_plan* p) {
 }
 
 // Zero-padded forward transform of time rows in[b][j][n] (j < nrows) into the spectra of the
-// batched products, out[l][j][b] with rows padded to nrows_pad: the register kernel for M = 256,
-// else the row transform.
+// batched products, out[l][j][b] with rows padded to nrows_pad by zeros.
 static hipError_t rfft_batch(const float* in, int B, int nrows, int nrows_pad, float2* out, int bp, const Geometry& g,
                              hipStream_t st) {
-  const int64_t slot = (int64_t)nrows_pad * bp;
-  if (g.M == 256) return launch_rfft_batch256(in, B, nrows, nrows_pad, out, bp, slot, g.nt, 1.0f, st);
-  return launch_rfft_rows(in, B, nrows, nrows_pad, out, 1, bp, slot, g, 1.0f, st);
+  if (g.M == 256)
+    return launch_rfft_batch256(in, B, nrows, nrows_pad, out, bp, (int64_t)nrows_pad * bp, g.nt, 1.0f, st);
+  return launch_rfft_units(in, g.nt, (int64_t)nrows * g.nt, nrows, nrows_pad, B, B, out, bp, 1,
+                           (int64_t)nrows_pad * bp, g, 1.0f, st);
 }
 
 // Sum of the split partials part[s][l][o][2 bp] of a batched product (times tau[l][b] when given)
-// and the inverse real FFT into out[b][o][n]: one fused kernel for M = 256, else the sum into
-// the spectra rows yh[b][o][l] and a row transform.
+// and the inverse real FFT into out[b][o][n].
 static hipError_t sum_and_irfft(const float* part, int splits, int noq, int nrows, int B, int bp, const float* tau,
-                                float2* yh, float* out, const Geometry& g, hipStream_t st) {
-  const float scale = 1.0f / (float)g.L;
-  if (g.M == 256) return launch_sum_irfft256(part, splits, noq, nrows, B, bp, tau, out, g.nt, scale, st);
-  hipError_t e = launch_sum_f(part, splits, g.M, noq, nrows, B, bp, tau, yh, st);
-  if (e == hipSuccess) e = launch_irfft_rows(yh, (int64_t)B * nrows, g.M, 1, out, g.nt, g, scale, st);
-  return e;
+                                float* out, const Geometry& g, hipStream_t st) {
+  if (g.M == 256)
+    return launch_sum_irfft256(part, splits, noq, nrows, B, bp, tau, out, g.nt, 1.0f / (float)g.L, st);
+  return launch_irfft_units((const float2*)part, splits, (int64_t)g.M * noq * bp, bp, 1, (int64_t)noq * bp, nrows, B,
+                            tau, bp, out, g.nt, (int64_t)nrows * g.nt, g, 1.0f / (float)g.L, st);
+}
+
+// Mid-chain of the batched paths; *groups (when given) is the count of partial maxima left in cmax.
+static hipError_t mid_chain(s2w_plan* p, float2* U, const float* scale, int B, int bp, bool adjoint, bool pack_bf16,
+                            hipStream_t st, float* cmax, int64_t cmax_floats, int* groups, const DispOut* disp) {
+  const Geometry& g = p->geo;
+  if (g.M == 256)
+    return launch_mid_batch256(U, scale, B, bp, adjoint, pack_bf16, g, st, p->tune.mid_rupts, cmax, cmax_floats, groups,
+                               disp);
+  return launch_mid_units(U, scale, B, bp, adjoint, pack_bf16, g, st, cmax, cmax_floats, groups, disp);
+}
+
+// One rupture's (or one operand's) time rows in[c][n] into the spectra out[c][l], c < npad, and back.
+static hipError_t rfft_single(const float* in, int nrows, int nrows_pad, float2* out, const Geometry& g,
+                              hipStream_t st) {
+  return launch_rfft_units(in, 0, g.nt, 1, 1, nrows, nrows_pad, out, 0, g.M, 1, g, 1.0f, st);
+}
+static hipError_t irfft_single(const float2* in, int nrows, float* out, const Geometry& g, hipStream_t st) {
+  return launch_irfft_units(in, 1, 0, 0, g.M, 1, 1, nrows, nullptr, 0, out, 0, g.nt, g, 1.0f / (float)g.L, st);
 }
 
 // Batched forward on the matrix cores (half-precision stores).
@@ -762,7 +775,6 @@ static s2w_status forward_half(s2w_plan* p, const float* s, int32_t B, float* y,
   float* tau_up = (float*)(p->ws + L.tau_up);
   float* tau_down = (float*)(p->ws + L.tau_down);
   float* part = (float*)(p->ws + L.part_f);
-  float2* yh = (float2*)(p->ws + L.yhb);
   const uint4* Gq = (const uint4*)(p->op + L.gq);
   const float* sG = (const float*)(p->op + L.sg);
   const uint4* Fq = (const uint4*)(p->op + L.fq);
@@ -806,15 +818,13 @@ static s2w_status forward_half(s2w_plan* p, const float* s, int32_t B, float* y,
   if (e == hipSuccess) e = mark(p->ev_end, st);
   if (e != hipSuccess) return hip_fail(p, e, "forward: elastic matrix-core stage");
   const bool fscale = h.kt_f != 1;
-  // float16 acoustic operands: the column scales come from maxima the mid-chain keeps as it
-  // writes (M = 256), else from a pass over U
+  // float16 acoustic operands: the column scales come from maxima the mid-chain keeps as it writes
   int groups = 0;
-  e = launch_mid_batch(U, sF, B, bp, false, fstaged, g, st, p->tune.mid_rupts, fscale ? part : nullptr,
+  e = mid_chain(p, U, sF, B, bp, false, fstaged, st, fscale ? part : nullptr,
                        part_floats(p), &groups, disp);
   if (e != hipSuccess) return hip_fail(p, e, "forward: mid-chain");
   if (fscale) {
-    e = groups > 0 ? launch_col_scale_final(part, groups, g.M, B, bp, tau_up, tau_down, st)
-                   : launch_col_scale(U, g.ngrid, g.M, B, bp, tau_up, tau_down, part, part_floats(p), st);
+    e = launch_col_scale_final(part, groups, g.M, B, bp, tau_up, tau_down, st);
     if (e != hipSuccess) return hip_fail(p, e, "forward: activation scale");
   }
   if (fstaged) {
@@ -825,7 +835,7 @@ static s2w_status forward_half(s2w_plan* p, const float* s, int32_t B, float* y,
                        g.M, h.noq, g.nobs, B, bp, splits, wide_re, st);
   }
   if (e != hipSuccess) return hip_fail(p, e, "forward: acoustic matrix-core stage");
-  e = sum_and_irfft(part, splits, h.noq, g.nobs, B, bp, fscale ? tau_down : nullptr, yh, y, g, st);
+  e = sum_and_irfft(part, splits, h.noq, g.nobs, B, bp, fscale ? tau_down : nullptr, y, g, st);
   if (e != hipSuccess) return hip_fail(p, e, "forward: output transform");
   return S2W_OK;
 }
@@ -861,7 +871,6 @@ static s2w_status forward_b32(s2w_plan* p, const float* s, int32_t B, float* y, 
   float2* S = (float2*)(p->ws + L.s32);
   float2* U = (float2*)(p->ws + L.u32);
   float* part = (float*)(p->ws + L.part32);
-  float2* yh = (float2*)(p->ws + L.yh32);
   const int bp = f.bp;
   // S[l][j][b]
   hipError_t e = rfft_batch(s, B, g.nsub, f.nsk, S, bp, g, st);
@@ -875,7 +884,7 @@ static s2w_status forward_b32(s2w_plan* p, const float* s, int32_t B, float* y, 
                        st);
   if (e == hipSuccess) e = mark(p->ev_end, st);
   if (e != hipSuccess) return hip_fail(p, e, "forward: elastic matrix-core stage");
-  e = launch_mid_batch(U, nullptr, B, bp, false, false, g, st, p->tune.mid_rupts, nullptr, 0, nullptr, disp);
+  e = mid_chain(p, U, nullptr, B, bp, false, false, st, nullptr, 0, nullptr, disp);
   if (e != hipSuccess) return hip_fail(p, e, "forward: mid-chain");
   // part[split][l][o][n] = sum_{g in split} Fs[l][o][g] V[g][l][b]
   const int cf = b32_cfg(p, B, true);
@@ -885,7 +894,7 @@ static s2w_status forward_b32(s2w_plan* p, const float* s, int32_t B, float* y, 
                      (int64_t)g.M * bp, bp, g.ngrid, B, bp, part, prow, (int64_t)f.nok * prow,
                      (int64_t)g.M * f.nok * prow, g.M, sf, st);
   if (e != hipSuccess) return hip_fail(p, e, "forward: acoustic matrix-core stage");
-  e = sum_and_irfft(part, sf, f.nok, g.nobs, B, bp, nullptr, yh, y, g, st);
+  e = sum_and_irfft(part, sf, f.nok, g.nobs, B, bp, nullptr, y, g, st);
   if (e != hipSuccess) return hip_fail(p, e, "forward: output transform");
   return S2W_OK;
 }
@@ -901,7 +910,6 @@ static s2w_status adjoint_b32(s2w_plan* p, const float* r, int32_t B, float* gs,
   float2* R = (float2*)(p->ws + L.s32);
   float2* W = (float2*)(p->ws + L.u32);
   float* part = (float*)(p->ws + L.part32);
-  float2* gh = (float2*)(p->ws + L.yh32);
   const int bp = f.bp;
   // R[l][o][b]
   hipError_t e = rfft_batch(r, B, g.nobs, f.nok, R, bp, g, st);
@@ -912,7 +920,7 @@ static s2w_status adjoint_b32(s2w_plan* p, const float* r, int32_t B, float* gs,
                      (int64_t)f.nok * bp, f.nok, B, bp, (float*)W, 2 * (int64_t)g.M * bp, 2 * (int64_t)bp, 0, g.M, 1,
                      st);
   if (e != hipSuccess) return hip_fail(p, e, "adjoint: acoustic matrix-core stage");
-  e = launch_mid_batch(W, nullptr, B, bp, true, false, g, st, p->tune.mid_rupts);
+  e = mid_chain(p, W, nullptr, B, bp, true, false, st, nullptr, 0, nullptr, nullptr);
   if (e != hipSuccess) return hip_fail(p, e, "adjoint: mid-chain");
   // part[split][l][j][n] = sum_{g in split} conj(Gs[g][l][j]) W'[g][l][b]
   // its own tile: by default 128 x 32 tiles from B = 9 to 64 (the subfault rows are many more
@@ -927,7 +935,7 @@ static s2w_status adjoint_b32(s2w_plan* p, const float* r, int32_t B, float* gs,
                        (int64_t)f.nsk * prow, (int64_t)g.M * f.nsk * prow, g.M, sa, st);
   if (e == hipSuccess) e = mark(p->ev_end, st);
   if (e != hipSuccess) return hip_fail(p, e, "adjoint: elastic matrix-core stage");
-  e = sum_and_irfft(part, sa, f.nsk, g.nsub, B, bp, nullptr, gh, gs, g, st);
+  e = sum_and_irfft(part, sa, f.nsk, g.nsub, B, bp, nullptr, gs, g, st);
   if (e != hipSuccess) return hip_fail(p, e, "adjoint: output transform");
   return S2W_OK;
 }
@@ -943,7 +951,6 @@ static s2w_status adjoint_half(s2w_plan* p, const float* r, int32_t B, float* gs
   float* part = (float*)(p->ws + L.part_f);
   float2* R = (float2*)part;                     // residual spectra R[l][o][b]
   float2* W = (float2*)(p->ws + L.U);            // W[g][l][b]
-  float2* gh = (float2*)(p->ws + L.S);           // rows gh[b][j][l]
   float* sig_up = (float*)(p->ws + L.sig_up);
   float* sig_down = (float*)(p->ws + L.sig_down);
   float* tau_up = (float*)(p->ws + L.tau_up);
@@ -967,11 +974,9 @@ static s2w_status adjoint_half(s2w_plan* p, const float* r, int32_t B, float* gs
                     (float*)W, 0, 2 * (int64_t)bp, 2 * (int64_t)g.M * bp, B, bp, g.M, 1, st);
   if (e != hipSuccess) return hip_fail(p, e, "adjoint: acoustic matrix-core stage");
   int groups = 0;
-  e = launch_mid_batch(W, sG, B, bp, true, false, g, st, p->tune.mid_rupts, sg16 ? part : nullptr, part_floats(p),
-                       &groups);
+  e = mid_chain(p, W, sG, B, bp, true, false, st, sg16 ? part : nullptr, part_floats(p), &groups, nullptr);
   if (e == hipSuccess && sg16)
-    e = groups > 0 ? launch_col_scale_final(part, groups, g.M, B, bp, tau_up, tau_down, st)
-                   : launch_col_scale(W, g.ngrid, g.M, B, bp, tau_up, tau_down, part, part_floats(p), st);
+    e = launch_col_scale_final(part, groups, g.M, B, bp, tau_up, tau_down, st);
   if (e != hipSuccess) return hip_fail(p, e, "adjoint: mid-chain");
   // part[split][l][j][n] = sum_{g in split} conj(G[g][l][j]) W'[g][l][b] (row-block-major store)
   const int64_t prow = 2 * (int64_t)bp;
@@ -994,7 +999,7 @@ static s2w_status adjoint_half(s2w_plan* p, const float* r, int32_t B, float* gs
                       (int64_t)h.nsq * prow, prow, B, bp, g.M, sa, st);
   if (e == hipSuccess) e = mark(p->ev_end, st);
   if (e != hipSuccess) return hip_fail(p, e, "adjoint: elastic matrix-core stage");
-  e = sum_and_irfft(part, sa, h.nsq, g.nsub, B, bp, nullptr, gh, gs, g, st);
+  e = sum_and_irfft(part, sa, h.nsq, g.nsub, B, bp, nullptr, gs, g, st);
   if (e != hipSuccess) return hip_fail(p, e, "adjoint: output transform");
   return S2W_OK;
 }
@@ -1194,11 +1199,10 @@ static s2w_status forward_single(s2w_plan* p, const float* s, int32_t B, float* 
   const bool fused = fused_forward_opt(g) <= 32;
   if (!fused && !Vh) return fail(p, S2W_EUNSUPPORTED, "forward: the unfused path needs the bound workspace");
   const int nwg = p->ncu * p->tune.fused_wg_per_cu;
-  const float inv_l = 1.0f / (float)g.L;
   for (int b = 0; b < B; ++b) {
     const float* sb = s + (int64_t)b * g.nsub * g.nt;
     float* yb = y + (int64_t)b * g.nobs * g.nt;
-    hipError_t e = launch_rfft_rows(sb, 1, g.nsub, g.nsp, Sh, 0, g.M, 1, g, 1.0f, st);
+    hipError_t e = rfft_single(sb, g.nsub, g.nsp, Sh, g, st);
     if (e != hipSuccess) return hip_fail(p, e, "forward: source transform");
     int nparts;
     DispOut db{};
@@ -1220,7 +1224,7 @@ static s2w_status forward_single(s2w_plan* p, const float* s, int32_t B, float* 
     if (e != hipSuccess) return hip_fail(p, e, "forward: contraction");
     e = launch_sum_parts(part, nparts, (int64_t)g.nop * g.M, yh, st);
     if (e != hipSuccess) return hip_fail(p, e, "forward: partial sum");
-    e = launch_irfft_rows(yh, g.nobs, g.M, 1, yb, g.nt, g, inv_l, st);
+    e = irfft_single(yh, g.nobs, yb, g, st);
     if (e != hipSuccess) return hip_fail(p, e, "forward: output transform");
   }
   return S2W_OK;
@@ -1243,11 +1247,10 @@ s2w_status s2w_adjoint(s2w_plan* p, const float* r, int32_t B, float* gs, void* 
   float2* part = (float2*)(p->ws + p->lay.part2);
   float2* gsh = (float2*)(p->ws + p->lay.gsh);
   const int nwg = p->ncu * p->tune.fused_wg_per_cu;
-  const float inv_l = 1.0f / (float)g.L;
   for (int b = 0; b < B; ++b) {
     const float* rb = r + (int64_t)b * g.nobs * g.nt;
     float* gb = gs + (int64_t)b * g.nsub * g.nt;
-    hipError_t e = launch_rfft_rows(rb, 1, g.nobs, g.nop, Rh, 0, g.M, 1, g, 1.0f, st);
+    hipError_t e = rfft_single(rb, g.nobs, g.nop, Rh, g, st);
     if (e != hipSuccess) return hip_fail(p, e, "adjoint: residual transform");
     e = launch_adjoint_rows(Fh, Rh, Wp, nwg, p->tune.fused_rows, g, st);
     if (e != hipSuccess) return hip_fail(p, e, "adjoint: acoustic stage");
@@ -1257,7 +1260,7 @@ s2w_status s2w_adjoint(s2w_plan* p, const float* r, int32_t B, float* gs, void* 
     if (e != hipSuccess) return hip_fail(p, e, "adjoint: elastic stage");
     e = launch_sum_parts(part, p->tune.adj_splits, (int64_t)g.nsp * g.M, gsh, st);
     if (e != hipSuccess) return hip_fail(p, e, "adjoint: partial sum");
-    e = launch_irfft_rows(gsh, g.nsub, g.M, 1, gb, g.nt, g, inv_l, st);
+    e = irfft_single(gsh, g.nsub, gb, g, st);
     if (e != hipSuccess) return hip_fail(p, e, "adjoint: output transform");
   }
   return S2W_OK;
@@ -1420,8 +1423,9 @@ s2w_status s2w_bltt_set_blocks(s2w_bltt* p, const float* F_chunk, int64_t row0, 
   const Geometry& g = p->geo;
   float2* Fs = (float2*)(p->op + p->o_fs);
   // Fs[row][l][c]: the GEMM layout of the forward product (c padded with zeros)
-  hipError_t e = launch_rfft_rows(F_chunk, nrows, p->desc.ncol, p->ncol_k, Fs + row0 * g.M * p->ncol_k,
-                                  (int64_t)g.M * p->ncol_k, 1, p->ncol_k, g, 1.0f, (hipStream_t)stream);
+  hipError_t e = launch_rfft_units(F_chunk, (int64_t)p->desc.ncol * g.nt, g.nt, (int)nrows, (int)nrows, p->desc.ncol,
+                                   p->ncol_k, Fs + row0 * g.M * p->ncol_k, (int64_t)g.M * p->ncol_k, 1, p->ncol_k, g,
+                                   1.0f, (hipStream_t)stream);
   if (e != hipSuccess) return bhip(p, e, "set_blocks: transform");
   for (int64_t r = row0; r < row0 + nrows; ++r)
     if (!p->row_set[(size_t)r]) {
@@ -1458,11 +1462,12 @@ s2w_status s2w_bltt_apply(s2w_bltt* p, const float* x, int32_t B, float* y, void
   if (B <= 4) {
     // few inputs: per-bin matrix-vector products streaming the store once (HBM-bound);
     // inputs transformed as S[b][l][c]
-    hipError_t e = launch_rfft_rows(x, B, ncol, p->ncol_k, S, (int64_t)g.M * p->ncol_k, 1, p->ncol_k, g, 1.0f, st);
+    hipError_t e = launch_rfft_units(x, (int64_t)ncol * g.nt, g.nt, B, B, ncol, p->ncol_k, S,
+                                     (int64_t)g.M * p->ncol_k, 1, p->ncol_k, g, 1.0f, st);
     if (e != hipSuccess) return bhip(p, e, "apply: input transform");
     e = launch_bltt_gemv(Fs, S, yh, nrow, g.M, p->ncol_k, B, p->ncu, st);
     if (e != hipSuccess) return bhip(p, e, "apply: per-bin products");
-    e = launch_irfft_rows(yh, (int64_t)B * nrow, g.M, 1, y, g.nt, g, 1.0f / (float)g.L, st);
+    e = irfft_single(yh, B * nrow, y, g, st);
     if (e != hipSuccess) return bhip(p, e, "apply: output transform");
     return S2W_OK;
   }
@@ -1477,7 +1482,7 @@ s2w_status s2w_bltt_apply(s2w_bltt* p, const float* x, int32_t B, float* y, void
                      S, bp, (int64_t)p->ncol_k * bp, p->ncol_k, B, bp, part, prow, (int64_t)p->nrow_k * prow,
                      (int64_t)g.M * p->nrow_k * prow, g.M, splits, st);
   if (e != hipSuccess) return bhip(p, e, "apply: matrix-core product");
-  e = sum_and_irfft(part, splits, p->nrow_k, nrow, B, bp, nullptr, yh, y, g, st);
+  e = sum_and_irfft(part, splits, p->nrow_k, nrow, B, bp, nullptr, y, g, st);
   if (e != hipSuccess) return bhip(p, e, "apply: output transform");
   return S2W_OK;
 }
@@ -1493,7 +1498,6 @@ s2w_status s2w_bltt_adjoint(s2w_bltt* p, const float* y, int32_t B, float* x, vo
   const float2* Fs = (const float2*)(p->op + p->o_fs);
   float2* R = (float2*)(p->ws + p->o_s);
   float* part = (float*)(p->ws + p->o_part);
-  float2* xh = (float2*)(p->ws + p->o_yh);
   // R[l][r][b] (rows padded with zeros)
   hipError_t e = rfft_batch(y, B, nrow, p->nrow_k, R, bp, g, st);
   if (e != hipSuccess) return bhip(p, e, "adjoint: input transform");
@@ -1505,7 +1509,7 @@ s2w_status s2w_bltt_adjoint(s2w_bltt* p, const float* y, int32_t B, float* x, vo
                      bp, (int64_t)p->nrow_k * bp, p->nrow_k, B, bp, part, prow, (int64_t)p->ncol_k * prow,
                      (int64_t)g.M * p->ncol_k * prow, g.M, splits, st);
   if (e != hipSuccess) return bhip(p, e, "adjoint: matrix-core product");
-  e = sum_and_irfft(part, splits, p->ncol_k, ncol, B, bp, nullptr, xh, x, g, st);
+  e = sum_and_irfft(part, splits, p->ncol_k, ncol, B, bp, nullptr, x, g, st);
   if (e != hipSuccess) return bhip(p, e, "adjoint: output transform");
   return S2W_OK;
 }

@@ -9,6 +9,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stdint.h>
 
 #include "s2w_internal.h"
@@ -18,8 +19,19 @@ namespace s2w {
 typedef float v4f __attribute__((ext_vector_type(4)));
 
 constexpr int TWN = 1024;  // largest transform length L supported
-// c_tw[k] = exp(-2 pi i k / TWN), k < TWN/2; rounded from double precision on the host.
-extern __constant__ float2 c_tw[TWN / 2];
+// c_tw[k] = exp(-2 pi i k / TWN), k < TWN/2; rounded from double precision on the host.  Each
+// source file that transforms holds its own copy (no relocatable device code); upload_tw_table
+// fills the copy of the including file on the current device.
+static __constant__ float2 c_tw[TWN / 2];
+
+static inline hipError_t upload_tw_table() {
+  float2 h[TWN / 2];
+  for (int k = 0; k < TWN / 2; ++k) {
+    const double a = -2.0 * M_PI * (double)k / (double)TWN;
+    h[k] = make_float2((float)cos(a), (float)sin(a));
+  }
+  return hipMemcpyToSymbol(HIP_SYMBOL(c_tw), h, sizeof(h), 0, hipMemcpyHostToDevice);
+}
 
 __device__ __forceinline__ float2 cadd(float2 a, float2 b) { return make_float2(a.x + b.x, a.y + b.y); }
 __device__ __forceinline__ float2 csub(float2 a, float2 b) { return make_float2(a.x - b.x, a.y - b.y); }
@@ -249,18 +261,6 @@ __device__ __forceinline__ float2* lds_midchain2(float2* X, float2* Y, int R, in
   __syncthreads();
   return V;
 }
-
-// Three-buffer form: result written to V (may alias U); bufA, bufB scratch.
-__device__ __forceinline__ void lds_midchain(const float2* U, float2* V, float2* bufA, float2* bufB, int R, int M,
-                                             int logM, int nt, int mode, float scale, const Twiddles& tw) {
-  const int n = R * M;
-  for (int i = threadIdx.x; i < n; i += blockDim.x) bufA[i] = U[i];
-  __syncthreads();
-  float2* res = lds_midchain2(bufA, bufB, R, M, logM, nt, mode, scale, tw);
-  for (int i = threadIdx.x; i < n; i += blockDim.x) V[i] = res[i];
-  __syncthreads();
-}
-
 
 // ---------------------------------------------------------------------------------------------
 // 256-point transforms in registers (the paper's L = 512: 256 packed slots), four-step form

@@ -16,110 +16,7 @@
 
 namespace s2w {
 
-__constant__ float2 c_tw[TWN / 2];
-
-hipError_t upload_twiddles(int device) {
-  (void)device;
-  static float2 h[TWN / 2];
-  for (int k = 0; k < TWN / 2; ++k) {
-    const double a = -2.0 * M_PI * (double)k / (double)TWN;
-    h[k] = make_float2((float)cos(a), (float)sin(a));
-  }
-  return hipMemcpyToSymbol(HIP_SYMBOL(c_tw), h, sizeof(h), 0, hipMemcpyHostToDevice);
-}
-
-static inline int rows_per_block(int M) { return M >= 4096 ? 1 : 4096 / M; }
-
-// ---------------------------------------------------------------------------------------------
-// Real rows -> packed spectra (zero-padded forward real FFT of length L = 2M, Alg. 2 steps 1-2).
-__global__ __launch_bounds__(256) void k_rfft_rows(const float* __restrict__ in, int64_t nrows, int ninner,
-                                                   int ninner_pad, float2* __restrict__ out, int64_t out_outer,
-                                                   int64_t out_inner, int64_t out_slot, int nt, int M, int logM,
-                                                   int R, float scale) {
-  extern __shared__ float2 smem[];
-  float2* A = smem;
-  float2* Bf = smem + R * M;
-  const Twiddles tw = lds_twiddles(smem + 2 * R * M, M);
-  const int64_t row0 = (int64_t)blockIdx.x * R;
-  for (int i = threadIdx.x; i < R * M; i += blockDim.x) {
-    const int r = i >> logM, p = i & (M - 1);
-    const int64_t row = row0 + r;
-    float2 v = make_float2(0.f, 0.f);
-    if (row < nrows) {
-      const int64_t o = row / ninner_pad;
-      const int inn = (int)(row - o * ninner_pad);
-      if (inn < ninner) {
-        const float* x = in + (o * ninner + inn) * (int64_t)nt;
-        const int m0 = 2 * p, m1 = 2 * p + 1;
-        v.x = m0 < nt ? x[m0] * scale : 0.f;
-        v.y = m1 < nt ? x[m1] * scale : 0.f;
-      }
-    }
-    A[i] = v;
-  }
-  __syncthreads();
-  float2* Z = lds_cfft(A, Bf, R, M, logM, -1, tw.c);
-  for (int i = threadIdx.x; i < R * M; i += blockDim.x) {
-    const int r = i % R, k = i / R;
-    const int64_t row = row0 + r;
-    if (row < nrows) {
-      const int64_t o = row / ninner_pad;
-      const int inn = (int)(row - o * ninner_pad);
-      out[o * out_outer + inn * out_inner + k * out_slot] = rfft_post(Z + r * M, k, M, tw.r);
-    }
-  }
-}
-
-hipError_t launch_rfft_rows(const float* in, int64_t nouter, int ninner, int ninner_pad, float2* out,
-                            int64_t out_outer, int64_t out_inner, int64_t out_slot, const Geometry& g, float scale,
-                            hipStream_t st) {
-  const int R = rows_per_block(g.M);
-  const int64_t nrows = nouter * ninner_pad;
-  if (nrows == 0) return hipSuccess;
-  const int64_t nblk = (nrows + R - 1) / R;
-  hipLaunchKernelGGL(k_rfft_rows, dim3((unsigned)nblk), dim3(256), (2 * R + 2) * g.M * sizeof(float2), st, in, nrows,
-                     ninner, ninner_pad, out, out_outer, out_inner, out_slot, g.nt, g.M, g.logM, R, scale);
-  return hipGetLastError();
-}
-
-// Packed spectra -> real rows (inverse real FFT, Alg. 2 steps 4-5: keep n < nt).
-__global__ __launch_bounds__(256) void k_irfft_rows(const float2* __restrict__ in, int64_t nrows, int64_t in_row,
-                                                    int64_t in_slot, float* __restrict__ out, int64_t out_row,
-                                                    int nt, int M, int logM, int R, float scale) {
-  extern __shared__ float2 smem[];
-  float2* X = smem;
-  float2* A = smem + R * M;
-  float2* Bf = smem + 2 * R * M;
-  const Twiddles tw = lds_twiddles(smem + 3 * R * M, M);
-  const int64_t row0 = (int64_t)blockIdx.x * R;
-  for (int i = threadIdx.x; i < R * M; i += blockDim.x) {
-    const int r = i % R, k = i / R;
-    const int64_t row = row0 + r;
-    X[r * M + k] = row < nrows ? in[row * in_row + k * in_slot] : make_float2(0.f, 0.f);
-  }
-  __syncthreads();
-  for (int i = threadIdx.x; i < R * M; i += blockDim.x) {
-    const int r = i >> logM, k = i & (M - 1);
-    A[i] = irfft_pre(X + r * M, k, M, tw.r);
-  }
-  __syncthreads();
-  float2* z = lds_cfft(A, Bf, R, M, logM, +1, tw.c);
-  for (int i = threadIdx.x; i < R * nt; i += blockDim.x) {
-    const int r = i / nt, m = i - r * nt;
-    const int64_t row = row0 + r;
-    if (row < nrows) out[row * out_row + m] = zsample(z + r * M, m) * scale;
-  }
-}
-
-hipError_t launch_irfft_rows(const float2* in, int64_t nrows, int64_t in_row, int64_t in_slot, float* out,
-                             int64_t out_row, const Geometry& g, float scale, hipStream_t st) {
-  if (nrows == 0) return hipSuccess;
-  const int R = rows_per_block(g.M);
-  const int64_t nblk = (nrows + R - 1) / R;
-  hipLaunchKernelGGL(k_irfft_rows, dim3((unsigned)nblk), dim3(256), (3 * R + 2) * g.M * sizeof(float2), st, in, nrows,
-                     in_row, in_slot, out, out_row, g.nt, g.M, g.logM, R, scale);
-  return hipGetLastError();
-}
+hipError_t upload_twiddles() { return upload_tw_table(); }
 
 // ---------------------------------------------------------------------------------------------
 // Contractions over the stored column index c (subfault j or observer o).
@@ -517,57 +414,6 @@ __device__ __forceinline__ void store_v(float2* dst, float2 v, float f) {
   }
 }
 
-// General M: rows staged through a padded transposition buffer, generic LDS transforms.
-template <int R, int PACK, bool DISP>
-__global__ __launch_bounds__(256) void k_mid_batch(float2* __restrict__ U, const float* __restrict__ sF, int ngrid,
-                                                   int B, int bp, int M, int logM, int nt, int mode, float mscale,
-                                                   DispOut disp) {
-  extern __shared__ float2 smem[];
-  // two buffers of M*(R+1) values: each serves as the row-major FFT buffer [R][M] and, while
-  // free, as the padded transposition buffer [M][R+1] (conflict-free in both directions)
-  const int BUF = M * (R + 1);
-  float2* X = smem;
-  float2* Y = X + BUF;
-  const Twiddles tw = lds_twiddles(Y + BUF, M);
-  const int nbb = (B + R - 1) / R;
-  const int64_t units = (int64_t)ngrid * nbb;
-  __shared__ short dtab[DISP ? 512 : 1];
-  if (DISP) {
-    disp_fill_cols(disp, nt, dtab);
-    __syncthreads();
-  }
-  for (int64_t u = blockIdx.x; u < units; u += gridDim.x) {
-    const int g = (int)(u / nbb);
-    const int b0 = (int)(u % nbb) * R;
-    const float2* src = U + (int64_t)g * M * bp + b0;
-    for (int i = threadIdx.x; i < R * M; i += blockDim.x) {
-      const int l = i / R, r = i % R;
-      Y[l * (R + 1) + r] = b0 + r < B ? src[(int64_t)l * bp + r] : make_float2(0.f, 0.f);
-    }
-    __syncthreads();
-    for (int i = threadIdx.x; i < R * M; i += blockDim.x) {
-      const int r = i >> logM, l = i & (M - 1);
-      X[i] = Y[l * (R + 1) + r];
-    }
-    __syncthreads();
-    const DispRows dr{disp.base + (int64_t)g * disp.grid_stride + (int64_t)b0 * disp.row_stride, disp.row_stride,
-                      B - b0, disp.scale};
-    const float2* V = lds_midchain2(X, Y, R, M, logM, nt, mode, mscale, tw, DISP ? &dr : nullptr, dtab);
-    float2* Tp = (V == X) ? Y : X;
-    for (int i = threadIdx.x; i < R * M; i += blockDim.x) {
-      const int r = i >> logM, l = i & (M - 1);
-      Tp[l * (R + 1) + r] = V[i];
-    }
-    __syncthreads();
-    float2* dst = U + (int64_t)g * M * bp + b0;
-    for (int i = threadIdx.x; i < R * M; i += blockDim.x) {
-      const int l = i / R, r = i % R;
-      if (b0 + r < B) store_v<PACK>(dst + (int64_t)l * bp + r, Tp[l * (R + 1) + r], sF ? sF[(int64_t)g * M + l] : 1.f);
-    }
-    __syncthreads();
-  }
-}
-
 // M = 256: 16 ruptures of one grid row per unit, the next unit's rows prefetched into
 // registers while the current one is transformed; rows kept with a padded stride (257) so
 // that the strided LDS writes and reads of the gather and scatter are conflict-free.
@@ -768,19 +614,25 @@ __global__ __launch_bounds__(256) void k_sum_irfft256(const float2* __restrict__
     {
       const int b = b0 + r;
       const int bc = b < B ? b : B - 1;  // loads unconditional, ruptures past B zeroed
-      const float2* src = part + (int64_t)o * bp + bc;
-#pragma unroll 4
+      // all loads of one split in flight together (one slot at a time, a chain of `splits` loads
+      // each, took 49 us at 64 rows of 16 ruptures and 8 splits); splits added in order
+      const float2* src = part + (int64_t)o * bp + bc + (int64_t)lq * noq * bp;
+      const int64_t k_stride = 16 * (int64_t)noq * bp;
+      float2 sum[16];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) sum[k] = src[k * k_stride];
+      for (int s = 1; s < splits; ++s) {
+        float2 w[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) w[k] = src[s * s_stride + k * k_stride];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) sum[k] = cadd(sum[k], w[k]);
+      }
+#pragma unroll
       for (int k = 0; k < 16; ++k) {
         const int l = lq + 16 * k;
-        const float2* p = src + (int64_t)l * noq * bp;
-        float re = 0.f, im = 0.f;
-        for (int s = 0; s < splits; ++s) {
-          const float2 v = p[s * s_stride];
-          re += v.x;
-          im += v.y;
-        }
         const float td = tau_down ? tau_down[(int64_t)l * bp + bc] : 1.f;
-        X[r * LD + l] = b < B ? make_float2(re * td, im * td) : make_float2(0.f, 0.f);
+        X[r * LD + l] = b < B ? make_float2(sum[k].x * td, sum[k].y * td) : make_float2(0.f, 0.f);
       }
     }
     __syncthreads();
@@ -827,67 +679,52 @@ hipError_t launch_sum_irfft256(const float* part, int splits, int noq, int nrows
   return hipGetLastError();
 }
 
-hipError_t launch_mid_batch(float2* U, const float* sF, int B, int bp, bool adjoint, bool pack_bf16,
-                            const Geometry& g, hipStream_t st, int rupts, float* cmax, int64_t cmax_floats,
-                            int* cmax_groups, const DispOut* disp) {
+hipError_t launch_mid_batch256(float2* U, const float* sF, int B, int bp, bool adjoint, bool pack_bf16,
+                               const Geometry& g, hipStream_t st, int rupts, float* cmax, int64_t cmax_floats,
+                               int* cmax_groups, const DispOut* disp) {
   if (cmax_groups) *cmax_groups = 0;
+  if (g.M != 256) return hipErrorInvalidValue;
   const DispOut dd = disp ? *disp : DispOut{};
-  constexpr int R = 16;
   const int mode = g.diff ? (adjoint ? MID_BACKWARD_T : MID_BACKWARD) : MID_NONE;
   const float mscale = (float)(1.0 / ((double)g.L * (g.diff ? (double)g.dt : 1.0)));
-  const int64_t units = (int64_t)g.ngrid * ((B + R - 1) / R);
-  const int64_t nblk = std::min<int64_t>(units, 256 * 8);
-  if (g.M == 256) {
-    // units of 16 or 32 ruptures of one grid row (32: 256-byte runs per slot, one 512-thread
-    // workgroup per CU)
-    const int ru = rupts == 32 ? 32 : 16;
-    const int nbb = (B + ru - 1) / ru;
-    const int64_t units256 = (int64_t)g.ngrid * nbb;
-    int64_t nb256 = std::min<int64_t>(units256, 256 * 8);
-    if (cmax) {
-      // whole groups of nbb workgroups, as many groups as the partial maxima fit
-      const int64_t gmax = cmax_floats / ((int64_t)g.M * bp);
-      int64_t groups = std::min<int64_t>(std::max<int64_t>(1, nb256 / nbb), gmax);
-      if (groups < 1) return hipErrorInvalidValue;
-      nb256 = groups * nbb;
-      if (cmax_groups) *cmax_groups = (int)groups;
-    }
-    if (B < 1 || g.nt > 256 || units256 > 0x7fffffff) return hipErrorInvalidValue;  // M = 256 implies nt <= 256
+  // units of 16 or 32 ruptures of one grid row (32: 256-byte runs per slot, one 512-thread
+  // workgroup per CU)
+  const int ru = rupts == 32 ? 32 : 16;
+  const int nbb = (B + ru - 1) / ru;
+  const int64_t units256 = (int64_t)g.ngrid * nbb;
+  int64_t nb256 = std::min<int64_t>(units256, 256 * 8);
+  if (cmax) {
+    // whole groups of nbb workgroups, as many groups as the partial maxima fit
+    const int64_t gmax = cmax_floats / ((int64_t)g.M * bp);
+    int64_t groups = std::min<int64_t>(std::max<int64_t>(1, nb256 / nbb), gmax);
+    if (groups < 1) return hipErrorInvalidValue;
+    nb256 = groups * nbb;
+    if (cmax_groups) *cmax_groups = (int)groups;
+  }
+  if (B < 1 || g.nt > 256 || units256 > 0x7fffffff) return hipErrorInvalidValue;  // M = 256 implies nt <= 256
 #define S2W_MID256K(P_, R_, D_, M_)                                                                              \
   hipLaunchKernelGGL((k_mid_batch256<P_, R_, D_, M_>), dim3((unsigned)nb256), dim3(16 * R_), 0, st, U, sF, g.ngrid, B, \
-                     bp, g.nt, mscale, cmax, dd)
-    // forward: packed or plain output, with or without displacement capture; adjoint: plain
+                   bp, g.nt, mscale, cmax, dd)
+  // forward: packed or plain output, with or without displacement capture; adjoint: plain
 #define S2W_MID256(P_, R_)                                                                                       \
   do {                                                                                                            \
-    if (adjoint) {                                                                                                \
-      if (mode == MID_BACKWARD_T) S2W_MID256K(0, R_, false, MID_BACKWARD_T);                                      \
-      else S2W_MID256K(0, R_, false, MID_NONE);                                                                   \
-    } else if (mode == MID_BACKWARD) {                                                                            \
-      if (dd.base) S2W_MID256K(P_, R_, true, MID_BACKWARD); else S2W_MID256K(P_, R_, false, MID_BACKWARD);        \
-    } else {                                                                                                      \
-      if (dd.base) S2W_MID256K(P_, R_, true, MID_NONE); else S2W_MID256K(P_, R_, false, MID_NONE);                \
-    }                                                                                                             \
+  if (adjoint) {                                                                                                \
+    if (mode == MID_BACKWARD_T) S2W_MID256K(0, R_, false, MID_BACKWARD_T);                                      \
+    else S2W_MID256K(0, R_, false, MID_NONE);                                                                   \
+  } else if (mode == MID_BACKWARD) {                                                                            \
+    if (dd.base) S2W_MID256K(P_, R_, true, MID_BACKWARD); else S2W_MID256K(P_, R_, false, MID_BACKWARD);        \
+  } else {                                                                                                      \
+    if (dd.base) S2W_MID256K(P_, R_, true, MID_NONE); else S2W_MID256K(P_, R_, false, MID_NONE);                \
+  }                                                                                                             \
   } while (0)
-    if (adjoint && (pack_bf16 || dd.base)) return hipErrorInvalidValue;
-    if (ru == 32) {
-      if (pack_bf16) S2W_MID256(1, 32); else S2W_MID256(0, 32);
-    } else {
-      if (pack_bf16) S2W_MID256(1, 16); else S2W_MID256(0, 16);
-    }
+  if (adjoint && (pack_bf16 || dd.base)) return hipErrorInvalidValue;
+  if (ru == 32) {
+    if (pack_bf16) S2W_MID256(1, 32); else S2W_MID256(0, 32);
+  } else {
+    if (pack_bf16) S2W_MID256(1, 16); else S2W_MID256(0, 16);
+  }
 #undef S2W_MID256
 #undef S2W_MID256K
-    return hipGetLastError();
-  }
-  const size_t lds = (2 * (size_t)g.M * (R + 1) + 2 * (size_t)g.M) * sizeof(float2);
-#define S2W_MIDG(P_, D_)                                                                                        \
-  hipLaunchKernelGGL((k_mid_batch<R, P_, D_>), dim3((unsigned)nblk), dim3(256), lds, st, U, sF, g.ngrid, B, bp, g.M, \
-                     g.logM, g.nt, mode, mscale, dd)
-  if (pack_bf16) {
-    if (dd.base) S2W_MIDG(1, true); else S2W_MIDG(1, false);
-  } else {
-    if (dd.base) S2W_MIDG(0, true); else S2W_MIDG(0, false);
-  }
-#undef S2W_MIDG
   return hipGetLastError();
 }
 

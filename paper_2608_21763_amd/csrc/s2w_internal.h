@@ -36,21 +36,35 @@ struct DispOut {
   uint32_t bits[16];    // steps 0 .. 511
 };
 
-// Twiddle table upload (once per device).
-hipError_t upload_twiddles(int device);
+// Twiddle table uploads to the current device (once per device), one per file that transforms.
+hipError_t upload_twiddles();
+hipError_t upload_twiddles_rows();
 
-// s[rows][nt] real rows (row = outer * ninner + inner, rows with inner >= ninner
-// are zero) -> packed spectra at out + outer*out_outer + inner*out_inner + slot*out_slot.
-hipError_t launch_rfft_rows(const float* in, int64_t nouter, int ninner, int ninner_pad, float2* out,
-                            int64_t out_outer, int64_t out_inner, int64_t out_slot, const Geometry& g, float scale,
-                            hipStream_t st);
-// Forward real FFT of time rows in[b][j][n] into out[l][j][b] (l * out_slot + j * bp + b), M = 256 only.
+// Row transforms (register transforms of s2w_rowfft.h), any M of the library.  Rows have an outer
+// index a and an inner index b; one of the far side's strides for b and for the slot is 1.
+// Zero-padded forward real FFT of in + a*in_a + b*in_b (rows a >= na or b >= nb are zero) into
+// out + a*oa + b*ob + l*ol for a < na_out, b < nb_out.
+hipError_t launch_rfft_units(const float* in, int64_t in_a, int64_t in_b, int na, int na_out, int nb, int nb_out,
+                             float2* out, int64_t oa, int64_t ob, int64_t ol, const Geometry& g, float scale,
+                             hipStream_t st);
+// Sum over splits of part + s*p_s + a*pa + b*pb + l*pl (times tau[l*tau_l + b] when given), inverse
+// real FFT, samples n < nt times scale at out + a*oa + b*ob.
+hipError_t launch_irfft_units(const float2* part, int splits, int64_t p_s, int64_t pa, int64_t pb, int64_t pl, int na,
+                              int nb, const float* tau, int64_t tau_l, float* out, int64_t oa, int64_t ob,
+                              const Geometry& g, float scale, hipStream_t st);
+// Half-precision setup: spectra of in[row][col][nt] as scaled half words (ht: 1 = bf16, 2 = f16) with
+// one power-of-two scale per (grid row, slot), down[(row0 + row)*M + l].  Elastic: row-block-major
+// words (((l*nrb + g/16)*(ncp/16) + c/16)*16 + g%16)*16 + c%16; else word c*w_col + l*w_slot + g,
+// with g = row0 + row and columns ncols <= c < ncp zero.  mx: scratch of at least M words.
+hipError_t launch_quant_spectra(int ht, bool elastic, const float* in, int64_t nrows, int ncols, int ncp,
+                                uint32_t* out, int64_t row0, int64_t w_col, int64_t w_slot, int nrb, float* down,
+                                uint32_t* mx, int64_t mx_words, const Geometry& g, hipStream_t st);
+// Batched forms of M = 256: the forward real FFT of time rows in[b][j][n] into out[l][j][b] (l * out_slot
+// + j * bp + b), and the sum of split partials part[s][l][o][2 bp] with the inverse into out[b][o][n].
 hipError_t launch_rfft_batch256(const float* in, int B, int nrows, int nrows_pad, float2* out, int bp, int64_t out_slot,
                                 int nt, float scale, hipStream_t st);
-
-// packed spectra rows (in + row*in_row + slot*in_slot) -> real rows out[row][n], n < nt, times scale
-hipError_t launch_irfft_rows(const float2* in, int64_t nrows, int64_t in_row, int64_t in_slot, float* out,
-                             int64_t out_row, const Geometry& g, float scale, hipStream_t st);
+hipError_t launch_sum_irfft256(const float* part, int splits, int noq, int nrows, int B, int bp,
+                               const float* tau_down, float* out, int nt, float scale, hipStream_t st);
 
 // Single-rupture fused forward: every workgroup contracts its grid rows against the
 // source spectrum, runs the mid-chain round trip in LDS and accumulates its partial
@@ -82,10 +96,6 @@ hipError_t launch_rows_acoustic(const float2* Fh, const float2* Vh, float2* part
                                 const Geometry& g, hipStream_t st);
 
 // ---- batched path (matrix cores, half-precision stores); ht: 1 = bf16, 2 = f16 ----
-// ng16 > 0 selects the row-block-major layout of the elastic store (ng16 = blocks of 16 grid
-// rows; sg, sl, sc unused): word (((l*ng16 + g/16)*(ncp/16) + c/16)*16 + g%16)*16 + c%16.
-hipError_t launch_quant_rows(int ht, const float2* staging, int64_t nrows, int M, int nc, int ncp, uint32_t* out,
-                             int64_t row0, int64_t sg, int64_t sl, int64_t sc, float* scale, int ng16, hipStream_t st);
 hipError_t launch_prep_act(int ht, int hterms, const float2* S, float* sig_up, float* sig_down, int M, int nsub,
                            int nsq, int B, int bp, int nks, int ncb, uint4* Bop, hipStream_t st);
 // Real-column activation fragments for the elastic GEMM tiles 17 and 18: Bre[l][ks][rcb][h][lane]
@@ -120,23 +130,19 @@ hipError_t launch_bltt_gemv(const float2* K, const float2* X, float2* yh, int nr
                             hipStream_t st);
 hipError_t launch_gemm_f2(const uint4* Fq, const uint2* V, float* part, int ngrid, int ngq, int M, int noq, int B,
                           int bp, int splits, hipStream_t st);
-// rupts: ruptures per unit of the M = 256 kernel (16 or 32; other values mean 16).  With cmax
-// (M = 256 only) the kernel also leaves per-(slot, rupture) maxima of |Re|, |Im| of what it
-// writes in cmax[group][l][b] (at most cmax_floats floats) and sets *cmax_groups to the group
-// count; elsewhere *cmax_groups is 0 and no maxima are produced.
-hipError_t launch_mid_batch(float2* U, const float* sF, int B, int bp, bool adjoint, bool pack_bf16,
-                            const Geometry& g, hipStream_t st, int rupts = 16, float* cmax = nullptr,
-                            int64_t cmax_floats = 0, int* cmax_groups = nullptr, const DispOut* disp = nullptr);
+// Batched mid-chain in place on U[g][l][b].  With cmax the kernel also leaves per-(slot, rupture)
+// maxima of |Re|, |Im| of what it writes in cmax[group][l][b] (at most cmax_floats floats) and sets
+// *cmax_groups to the group count.  M = 256 (rupts: ruptures per unit, 16 or 32; other values mean
+// 16) and every other M.
+hipError_t launch_mid_batch256(float2* U, const float* sF, int B, int bp, bool adjoint, bool pack_bf16,
+                               const Geometry& g, hipStream_t st, int rupts, float* cmax, int64_t cmax_floats,
+                               int* cmax_groups, const DispOut* disp);
+hipError_t launch_mid_units(float2* U, const float* sF, int B, int bp, bool adjoint, bool pack_bf16,
+                            const Geometry& g, hipStream_t st, float* cmax, int64_t cmax_floats, int* cmax_groups,
+                            const DispOut* disp);
 // Power-of-two column scales from partial maxima part[s][l][b], s < splits (columns b >= B get 1).
 hipError_t launch_col_scale_final(const float* part, int splits, int M, int B, int bp, float* tau_up, float* tau_down,
                                   hipStream_t st);
-hipError_t launch_col_scale(const float2* V, int ngrid, int M, int B, int bp, float* tau_up, float* tau_down,
-                            float* part, int64_t part_floats, hipStream_t st);
-hipError_t launch_sum_f(const float* part, int splits, int M, int noq, int nobs, int B, int bp, const float* tau_down,
-                        float2* yh, hipStream_t st);
-// Sum of split partials part[s][l][o][2 bp] and inverse real FFT into out[b][o][n] (M = 256 only).
-hipError_t launch_sum_irfft256(const float* part, int splits, int noq, int nrows, int B, int bp,
-                               const float* tau_down, float* out, int nt, float scale, hipStream_t st);
 hipError_t launch_zero_strided(uint32_t* out, int64_t n, int64_t stride, int width, hipStream_t st);
 hipError_t launch_act_scale(const float2* S, int M, int nk, int nkp, int B, int bp, float* sig_up, float* sig_down,
                             hipStream_t st);

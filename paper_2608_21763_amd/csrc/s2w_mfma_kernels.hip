@@ -29,63 +29,6 @@
 namespace s2w {
 
 // ---------------------------------------------------------------------------------------------
-// Setup: quantize rows of float32 spectra.  staging[r][l][c] (complex, c < ncp stored, c < nc
-// valid) -> out + (row0 + r)*sg + l*sl + c*sc (32-bit words), scale[(row0 + r)*M + l].
-// One block per (r, l): the scale is a power of two mapping the row's largest |re|, |im| into
-// [2^14, 2^15).
-template <int HT>
-__global__ __launch_bounds__(256) void k_quant_rows(const float2* __restrict__ staging, int M, int nc, int ncp,
-                                                    uint32_t* __restrict__ out, int64_t row0, int64_t sg, int64_t sl,
-                                                    int64_t sc, float* __restrict__ scale, int ng16) {
-  __shared__ float red[256];
-  const int r = blockIdx.x / M, l = blockIdx.x % M;
-  const float2* row = staging + ((int64_t)r * M + l) * ncp;
-  float mx = 0.f;
-  for (int c = threadIdx.x; c < nc; c += 256) {
-    const float2 v = row[c];
-    mx = fmaxf(mx, fmaxf(fabsf(v.x), fabsf(v.y)));
-  }
-  red[threadIdx.x] = mx;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (threadIdx.x < s) red[threadIdx.x] = fmaxf(red[threadIdx.x], red[threadIdx.x + s]);
-    __syncthreads();
-  }
-  float up, down;
-  pow2_scale(red[0], up, down);
-  const int64_t g = row0 + r;
-  if (threadIdx.x == 0) scale[g * M + l] = down;
-  if (ng16 > 0) {
-    // row-block-major store: word (((l * ng16 + g / 16) * (ncp / 16) + c / 16) * 16 + g % 16) * 16 + c % 16
-    uint32_t* o = out + (((int64_t)l * ng16 + (g >> 4)) * (ncp >> 4) * 16 + (g & 15)) * 16;
-    for (int c = threadIdx.x; c < ncp; c += 256) {
-      const float2 v = c < nc ? row[c] : make_float2(0.f, 0.f);
-      o[(int64_t)(c >> 4) * 256 + (c & 15)] = pack_half2<HT>(v.x * up, v.y * up);
-    }
-    return;
-  }
-  uint32_t* o = out + g * sg + (int64_t)l * sl;
-  for (int c = threadIdx.x; c < ncp; c += 256) {
-    const float2 v = c < nc ? row[c] : make_float2(0.f, 0.f);
-    o[(int64_t)c * sc] = to_half_bits<HT>(v.x * up) | (to_half_bits<HT>(v.y * up) << 16);
-  }
-}
-
-hipError_t launch_quant_rows(int ht, const float2* staging, int64_t nrows, int M, int nc, int ncp, uint32_t* out,
-                             int64_t row0, int64_t sg, int64_t sl, int64_t sc, float* scale, int ng16, hipStream_t st) {
-  if (nrows == 0) return hipSuccess;
-  if (ng16 > 0 && (ncp % 16)) return hipErrorInvalidValue;
-  dim3 grid((unsigned)(nrows * M));
-  if (ht == 1)
-    hipLaunchKernelGGL(k_quant_rows<1>, grid, dim3(256), 0, st, staging, M, nc, ncp, out, row0, sg, sl, sc, scale,
-                       ng16);
-  else
-    hipLaunchKernelGGL(k_quant_rows<2>, grid, dim3(256), 0, st, staging, M, nc, ncp, out, row0, sg, sl, sc, scale,
-                       ng16);
-  return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------------------------
 // Activation scales: sig[l][b] = power of two mapping max_j |S[l][j][b]| (re, im) into
 // [2^14, 2^15) (the inverse is applied to the GEMM result).  S is [l][nsq][bp] complex.
 // Workgroup of 16 columns (l, b..b+15) x 16 row groups: thread (jg, c) takes rows j = jg, jg +
@@ -882,38 +825,10 @@ hipError_t launch_act_scale(const float2* S, int M, int nk, int nkp, int B, int 
   return hipGetLastError();
 }
 
-// Column scales of the acoustic GEMM's activation (float16 operands only): for each (l, b),
-// a power of two mapping max_g |V[g][l][b]| (re, im) into [2^14, 2^15).  First pass: partial
-// maxima part[s][l][b] over grid-row ranges s (many workgroups, four loads in flight per
-// thread); second pass: the maximum over the ranges and the scale.
-__global__ __launch_bounds__(256) void k_col_max(const float2* __restrict__ V, int ngrid, int M, int B, int bp,
-                                                 int splits, float* __restrict__ part) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int s = blockIdx.y;
-  if (i >= (int64_t)M * bp) return;
-  const int l = (int)(i / bp), b = (int)(i - (int64_t)l * bp);
-  const int g0 = (int)((int64_t)ngrid * s / splits), g1 = (int)((int64_t)ngrid * (s + 1) / splits);
-  float m0 = 0.f, m1 = 0.f, m2 = 0.f, m3 = 0.f;
-  if (b < B) {
-    const float2* v = V + (int64_t)l * bp + b;
-    const int64_t gs = (int64_t)M * bp;
-    int g = g0;
-    for (; g + 4 <= g1; g += 4) {
-      const float2 x0 = v[(int64_t)g * gs], x1 = v[(int64_t)(g + 1) * gs];
-      const float2 x2 = v[(int64_t)(g + 2) * gs], x3 = v[(int64_t)(g + 3) * gs];
-      m0 = fmaxf(m0, fmaxf(fabsf(x0.x), fabsf(x0.y)));
-      m1 = fmaxf(m1, fmaxf(fabsf(x1.x), fabsf(x1.y)));
-      m2 = fmaxf(m2, fmaxf(fabsf(x2.x), fabsf(x2.y)));
-      m3 = fmaxf(m3, fmaxf(fabsf(x3.x), fabsf(x3.y)));
-    }
-    for (; g < g1; ++g) {
-      const float2 x = v[(int64_t)g * gs];
-      m0 = fmaxf(m0, fmaxf(fabsf(x.x), fabsf(x.y)));
-    }
-  }
-  part[(int64_t)s * M * bp + i] = fmaxf(fmaxf(m0, m1), fmaxf(m2, m3));
-}
-
+// Column scales of a product's activation (float16 operands only): for each (l, b), the power of
+// two mapping max_g |V[g][l][b]| (re, im) into [2^14, 2^15), from the mid-chain's partial maxima
+// part[s][l][b].
+//
 // The mid-chain leaves up to 2048 partial maxima per column.  A workgroup takes 16 columns, 16 threads
 // to a column with four loads in flight each (a chain of loads is what bounds it: one thread per
 // column took 830 us over 2048 partials of 16,384 columns, this 28 us).
@@ -945,21 +860,6 @@ __global__ __launch_bounds__(256) void k_col_scale_final(const float* __restrict
   }
 }
 
-hipError_t launch_col_scale(const float2* V, int ngrid, int M, int B, int bp, float* tau_up, float* tau_down,
-                            float* part, int64_t part_floats, hipStream_t st) {
-  const int64_t n = (int64_t)M * bp;
-  const int64_t nblk = (n + 255) / 256;
-  int splits = (int)std::max<int64_t>(1, std::min<int64_t>(64, 8192 / std::max<int64_t>(1, nblk)));
-  splits = std::min(splits, std::max(1, ngrid));
-  while (splits > 1 && (int64_t)splits * n > part_floats) --splits;
-  if ((int64_t)splits * n > part_floats) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_col_max, dim3((unsigned)nblk, (unsigned)splits), dim3(256), 0, st, V, ngrid, M, B, bp, splits,
-                     part);
-  hipLaunchKernelGGL(k_col_scale_final, dim3((unsigned)((n + 15) / 16)), dim3(256), 0, st, part, splits, n, B, bp, tau_up,
-                     tau_down);
-  return hipGetLastError();
-}
-
 hipError_t launch_col_scale_final(const float* part, int splits, int M, int B, int bp, float* tau_up, float* tau_down,
                                   hipStream_t st) {
   const int64_t n = (int64_t)M * bp;
@@ -980,34 +880,6 @@ hipError_t launch_zero_strided(uint32_t* out, int64_t n, int64_t stride, int wid
   const int64_t tot = n * width;
   if (tot == 0) return hipSuccess;
   hipLaunchKernelGGL(k_zero_strided, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, out, n, stride, width);
-  return hipGetLastError();
-}
-
-// Sum the acoustic partials over splits, undo the activation scale, and lay the result out
-// as rows yh[b][o][l] (complex) for the inverse transform.
-__global__ __launch_bounds__(256) void k_sum_f(const float* __restrict__ part, int splits, int M, int noq, int nobs,
-                                               int B, int bp, const float* __restrict__ tau_down, float2* __restrict__ yh) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;  // over (l, o, b)
-  const int64_t total = (int64_t)M * nobs * B;
-  if (i >= total) return;
-  const int b = (int)(i % B);
-  const int64_t q = i / B;
-  const int o = (int)(q % nobs), l = (int)(q / nobs);
-  float re = 0.f, im = 0.f;
-  for (int s = 0; s < splits; ++s) {
-    const float* p = part + (((int64_t)s * M + l) * noq + o) * (2 * bp) + 2 * b;
-    re += p[0];
-    im += p[1];
-  }
-  const float td = tau_down ? tau_down[(int64_t)l * bp + b] : 1.f;
-  yh[((int64_t)b * nobs + o) * M + l] = make_float2(re * td, im * td);
-}
-
-hipError_t launch_sum_f(const float* part, int splits, int M, int noq, int nobs, int B, int bp, const float* tau_down,
-                        float2* yh, hipStream_t st) {
-  const int64_t total = (int64_t)M * nobs * B;
-  hipLaunchKernelGGL(k_sum_f, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, part, splits, M, noq, nobs, B,
-                     bp, tau_down, yh);
   return hipGetLastError();
 }
 
