@@ -208,7 +208,8 @@ s2w_status s2w_forward_noalloc(s2w_plan* plan, const float* s, int32_t B, float*
 typedef struct s2w_tuning {
   int32_t fused_wg_per_cu;   /* single-rupture fused kernel: workgroups per compute unit (1..4) */
   int32_t fused_rows;        /* single-rupture fused kernel: grid rows per tile (4 or 8) */
-  int32_t adj_cols;          /* grid-row contractions (adjoint elastic stage): columns per thread (8 or 16) */
+  int32_t adj_cols;          /* grid-row contractions (adjoint elastic stage): columns per thread (8 or 16); until this
+                              * or adj_splits is set, both are chosen from the sizes */
   int32_t adj_splits;        /* single-rupture adjoint: grid splits of the transposed elastic stage */
   int32_t batch_path_min_b;  /* reserved: ignored (the layout, fixed at plan creation, picks the path) */
   int32_t gemm_cfg;          /* batched elastic GEMM tile, 256 grid rows tall, persistent workgroups:

@@ -115,6 +115,7 @@ struct s2w_plan {
   DirectGeo dg;
   Layout lay;
   s2w_tuning tune;
+  bool adj_set = false;          // the caller chose adj_cols or adj_splits
   char* op = nullptr;
   char* ws = nullptr;
   uint64_t op_bytes = 0, ws_bytes = 0;
@@ -524,6 +525,7 @@ s2w_status s2w_set_tuning(s2w_plan* p, const s2w_tuning* t) {
     if (t->adj_splits < 1 || t->adj_splits > kMaxSplits) return fail(p, S2W_EINVAL, "tuning: adj_splits");
     n.adj_splits = t->adj_splits;
   }
+  const bool adj_set = t->adj_cols || t->adj_splits;
   if (t->gemm_cfg) {
     const int c = t->gemm_cfg;
     if (!(c == -1 || c == 4 || c == 10 || c == 12 || (c >= 16 && c <= 18) || c == 24))
@@ -575,6 +577,7 @@ s2w_status s2w_set_tuning(s2w_plan* p, const s2w_tuning* t) {
     n.hadj_tile_g = t->hadj_tile_g < 0 ? -1 : t->hadj_tile_g - 1;
   }
   p->tune = n;
+  p->adj_set = p->adj_set || adj_set;
   return S2W_OK;
 }
 
@@ -1199,6 +1202,8 @@ static s2w_status forward_single(s2w_plan* p, const float* s, int32_t B, float* 
   const bool fused = fused_forward_opt(g) <= 32;
   if (!fused && !Vh) return fail(p, S2W_EUNSUPPORTED, "forward: the unfused path needs the bound workspace");
   const int nwg = p->ncu * p->tune.fused_wg_per_cu;
+  int cols = p->adj_set ? p->tune.adj_cols : 0, splits = p->tune.adj_splits;
+  rows_contract_shape(g.nop, g.ngrid, kMaxSplits, g, &cols, &splits);
   for (int b = 0; b < B; ++b) {
     const float* sb = s + (int64_t)b * g.nsub * g.nt;
     float* yb = y + (int64_t)b * g.nobs * g.nt;
@@ -1218,8 +1223,8 @@ static s2w_status forward_single(s2w_plan* p, const float* s, int32_t B, float* 
     } else {
       if (e == hipSuccess) e = launch_forward_rows(Gh, Sh, Vh, nwg, g, st, db);
       if (e == hipSuccess) e = mark(p->ev_end, st);
-      if (e == hipSuccess) e = launch_rows_acoustic(Fh, Vh, part, p->tune.adj_cols, p->tune.adj_splits, g, st);
-      nparts = p->tune.adj_splits;
+      if (e == hipSuccess) e = launch_rows_acoustic(Fh, Vh, part, cols, splits, g, st);
+      nparts = splits;
     }
     if (e != hipSuccess) return hip_fail(p, e, "forward: contraction");
     e = launch_sum_parts(part, nparts, (int64_t)g.nop * g.M, yh, st);
@@ -1247,6 +1252,8 @@ s2w_status s2w_adjoint(s2w_plan* p, const float* r, int32_t B, float* gs, void* 
   float2* part = (float2*)(p->ws + p->lay.part2);
   float2* gsh = (float2*)(p->ws + p->lay.gsh);
   const int nwg = p->ncu * p->tune.fused_wg_per_cu;
+  int cols = p->adj_set ? p->tune.adj_cols : 0, splits = p->tune.adj_splits;
+  rows_contract_shape(g.nsp, g.ngrid, kMaxSplits, g, &cols, &splits);
   for (int b = 0; b < B; ++b) {
     const float* rb = r + (int64_t)b * g.nobs * g.nt;
     float* gb = gs + (int64_t)b * g.nsub * g.nt;
@@ -1255,10 +1262,10 @@ s2w_status s2w_adjoint(s2w_plan* p, const float* r, int32_t B, float* gs, void* 
     e = launch_adjoint_rows(Fh, Rh, Wp, nwg, p->tune.fused_rows, g, st);
     if (e != hipSuccess) return hip_fail(p, e, "adjoint: acoustic stage");
     e = mark(p->ev_begin, st);
-    if (e == hipSuccess) e = launch_adjoint_elastic(Gh, Wp, part, p->tune.adj_cols, p->tune.adj_splits, g, st);
+    if (e == hipSuccess) e = launch_adjoint_elastic(Gh, Wp, part, cols, splits, g, st);
     if (e == hipSuccess) e = mark(p->ev_end, st);
     if (e != hipSuccess) return hip_fail(p, e, "adjoint: elastic stage");
-    e = launch_sum_parts(part, p->tune.adj_splits, (int64_t)g.nsp * g.M, gsh, st);
+    e = launch_sum_parts(part, splits, (int64_t)g.nsp * g.M, gsh, st);
     if (e != hipSuccess) return hip_fail(p, e, "adjoint: partial sum");
     e = irfft_single(gsh, g.nsub, gb, g, st);
     if (e != hipSuccess) return hip_fail(p, e, "adjoint: output transform");

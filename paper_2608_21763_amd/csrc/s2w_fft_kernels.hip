@@ -325,8 +325,14 @@ hipError_t launch_forward_rows(const float2* Gh, const float2* Sh, float2* Vh, i
 //   CONJ = false: part[split][c][l] = sum_{g in split} X[g][c][l] W[g][l]
 //                 (unfused forward, eq. 2 per bin; c = observer)
 // Workgroup (column block of CB columns, split).  Thread (cs, p): slot pair p, columns
-// c0 + cs + CS*i.  W[g] for the thread's slot pair is reused across its columns.
-template <int CPT, bool CONJ>
+// c0 + cs + CS*i, i < CPT.  W[g] for the thread's slot pair is reused across its columns.
+//
+// Bound by HBM: RU rows of CPT float4 per thread at a time, the next ones loaded under the products of
+// the current ones (loads past the range repeat its last row with a zero coefficient).  Sixteen
+// columns, one row and 16 ranges leave most CUs without work when the columns are few (60 columns:
+// 32 workgroups, 1.7 TB/s); 8 columns, two rows and more ranges: 60 x 30,207 x 256 steps 2.23 -> 0.58 ms,
+// 240 x 9,440 0.87 -> 0.70 ms.
+template <int CPT, int RU, bool CONJ>
 __global__ __launch_bounds__(256) void k_rows_contract(const v4f* __restrict__ X, const float2* __restrict__ W,
                                                        v4f* __restrict__ part, int ngrid, int nc, int ncp, int M) {
   const int NP = M >> 1, CS = 256 / NP;
@@ -341,15 +347,49 @@ __global__ __launch_bounds__(256) void k_rows_contract(const v4f* __restrict__ X
 #pragma unroll
   for (int i = 0; i < CPT; ++i) acc[i] = v4f{0.f, 0.f, 0.f, 0.f};
   const int64_t row_stride = (int64_t)ncp * NP;
-  for (int g = r0; g < r1; ++g) {
-    const float2 wa = W[(int64_t)g * M + 2 * p], wb = W[(int64_t)g * M + 2 * p + 1];
-    const Coef ka = make_coef(wa, dc, CONJ), kb = make_coef(wb, false, CONJ);
-    const v4f* xg = X + (int64_t)g * row_stride + p;
-    v4f x[CPT];
+  const v4f* W4 = reinterpret_cast<const v4f*>(W) + p;  // slots 2p, 2p + 1
+  const v4f* xc[CPT];
 #pragma unroll
-    for (int i = 0; i < CPT; ++i) x[i] = __builtin_nontemporal_load(xg + (int64_t)min(c0 + cs + CS * i, ncp - 1) * NP);
+  for (int i = 0; i < CPT; ++i) xc[i] = X + p + (int64_t)min(c0 + cs + CS * i, ncp - 1) * NP;
+  // the next rows are loaded under the products of the current ones; every load is unconditional
+  struct Rows {
+    v4f w[RU], x[RU][CPT];
+  };
+  auto load = [&](int g, Rows& q) {
 #pragma unroll
-    for (int i = 0; i < CPT; ++i) cmac2(acc[i], x[i], ka, kb);
+    for (int u = 0; u < RU; ++u) {
+      const int64_t gu = min(g + u, r1 - 1);
+      q.w[u] = W4[gu * NP];
+#pragma unroll
+      for (int i = 0; i < CPT; ++i) q.x[u][i] = __builtin_nontemporal_load(xc[i] + gu * row_stride);
+    }
+  };
+  auto use = [&](int g, const Rows& q) {
+#pragma unroll
+    for (int u = 0; u < RU; ++u) {
+      const bool ok = RU == 1 || g + u < r1;
+      const float2 wa = ok ? make_float2(q.w[u].x, q.w[u].y) : make_float2(0.f, 0.f);
+      const float2 wb = ok ? make_float2(q.w[u].z, q.w[u].w) : make_float2(0.f, 0.f);
+      const Coef ka = make_coef(wa, dc, CONJ), kb = make_coef(wb, false, CONJ);
+#pragma unroll
+      for (int i = 0; i < CPT; ++i) cmac2(acc[i], q.x[u][i], ka, kb);
+    }
+  };
+  if constexpr (RU == 1) {  // 64 registers of one row: the compiler's own pipelining is as good
+    for (int g = r0; g < r1; ++g) {
+      Rows cur;
+      load(g, cur);
+      use(g, cur);
+    }
+  } else if (r0 < r1) {
+    Rows cur, nxt;
+    load(r0, cur);
+    for (int g = r0; g < r1; g += 2 * RU) {
+      load(g + RU, nxt);
+      use(g, cur);
+      load(g + 2 * RU, cur);
+      if (g + RU < r1) use(g + RU, nxt);
+    }
   }
   v4f* pw = part + (int64_t)split * ncp * NP + p;
 #pragma unroll
@@ -359,19 +399,35 @@ __global__ __launch_bounds__(256) void k_rows_contract(const v4f* __restrict__ X
   }
 }
 
+// Columns per thread and row ranges where the caller has not set them (cols = 0), towards 240
+// workgroups (more ranges only add partial sums: 963 columns at 16, 32 and 64 ranges 1.52, 1.59,
+// 1.70 ms per adjoint of 4,720 rows): sixteen columns and 16 ranges where those give as many (480
+// columns 1.47 against 1.49-1.52 ms with 8, 963 columns 1.52 against 1.56), else 8 columns (240 columns
+// 0.80 against 0.96), and 4 where 8 with every range allowed still gives fewer (60 columns of 128
+// slots 0.18 against 0.21 ms).
+void rows_contract_shape(int ncp, int ngrid, int max_splits, const Geometry& g, int* cols, int* splits) {
+  if (*cols) return;
+  const int CS = 256 / (g.M / 2);
+  auto blocks = [&](int c) { return (ncp + c * CS - 1) / (c * CS); };
+  *cols = blocks(16) * 16 >= 240 ? 16 : (blocks(8) * max_splits >= 240 ? 8 : 4);
+  const int want = *cols == 16 ? 16 : std::max(16, (240 + blocks(*cols) - 1) / blocks(*cols));
+  *splits = std::max(1, std::min(std::min(max_splits, want), (ngrid + 3) / 4));
+}
+
 template <bool CONJ>
 static hipError_t rows_contract_t(const float2* X, const float2* W, float2* part, int cols_per_thread, int splits,
                                   int nc, int ncp, const Geometry& g, hipStream_t st) {
   const int CS = 256 / (g.M / 2);
-  const int CPT = cols_per_thread >= 16 ? 16 : 8;
+  const int CPT = cols_per_thread >= 16 ? 16 : (cols_per_thread >= 8 ? 8 : 4);
   const int CB = CS * CPT;
   dim3 grid((ncp + CB - 1) / CB, splits);
-  if (CPT == 16)
-    hipLaunchKernelGGL((k_rows_contract<16, CONJ>), grid, dim3(256), 0, st, (const v4f*)X, W, (v4f*)part, g.ngrid, nc,
-                       ncp, g.M);
-  else
-    hipLaunchKernelGGL((k_rows_contract<8, CONJ>), grid, dim3(256), 0, st, (const v4f*)X, W, (v4f*)part, g.ngrid, nc,
-                       ncp, g.M);
+#define S2W_RC(C_, R_)                                                                                                 \
+  hipLaunchKernelGGL((k_rows_contract<C_, R_, CONJ>), grid, dim3(256), 0, st, (const v4f*)X, W, (v4f*)part, g.ngrid, nc, \
+                     ncp, g.M)
+  if (CPT == 16) S2W_RC(16, 1);
+  else if (CPT == 8) S2W_RC(8, 2);
+  else S2W_RC(4, 4);
+#undef S2W_RC
   return hipGetLastError();
 }
 

@@ -88,6 +88,9 @@ hipError_t launch_adjoint_rows(const float2* Fh, const float2* Rh, float2* Wp, i
 hipError_t launch_adjoint_elastic(const float2* Gh, const float2* Wp, float2* part, int cols_per_thread, int splits,
                                   const Geometry& g, hipStream_t st);
 
+// Columns per thread and row ranges of a contraction over the grid rows, where *cols is 0.
+void rows_contract_shape(int ncp, int ngrid, int max_splits, const Geometry& g, int* cols, int* splits);
+
 // Unfused forward: stage 1 writes the per-row mid-chain output Vh[g][l]; stage 2
 // contracts it with the acoustic store per bin, split over grid rows.
 hipError_t launch_forward_rows(const float2* Gh, const float2* Sh, float2* Vh, int nwg, const Geometry& g,
