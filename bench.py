@@ -52,6 +52,7 @@ KERNEL_SOURCES = {
     "k_fused_forward": ["s2w_fft_kernels.hip", "s2w_device.h"],
     "k_mid_batch256": ["s2w_fft_kernels.hip", "s2w_device.h"],
     "k_gemm_g": ["s2w_mfma_kernels.hip", "s2w_half.h"],
+    "k_gemm_gs": ["s2w_mfma_stream_kernels.hip", "s2w_half.h"],
     "k_gemm_g4": ["s2w_mfma_kernels.hip", "s2w_half.h"],
     "k_gemm_f2": ["s2w_mfma_kernels.hip", "s2w_half.h"],
     "k_gemm_t2": ["s2w_mfma_adj_kernels.hip", "s2w_half.h", "s2w_half_re.h"],
@@ -99,8 +100,11 @@ def effective_tile(cfg: int, B: int, converted: bool) -> int:
     return 12 if B <= 64 else 18
 
 
-def elastic_kernel(cfg: int) -> str:
-    """Kernel of the batched half-precision elastic GEMM for tile setting `cfg` (-1 automatic)."""
+def elastic_kernel(cfg: int, B: int, bf16_products: bool) -> str:
+    """Kernel of the batched half-precision elastic GEMM for tile setting `cfg` (-1 automatic: streamed
+    for up to six 16-column blocks of activation terms)."""
+    if cfg == -1 and B <= 32 and (2 if bf16_products else 1) * ((2 * B + 15) // 16) <= 6:
+        return "k_gemm_gs"
     return "k_gemm_g" if cfg == 4 else "k_gemm_g4"
 
 
@@ -470,7 +474,7 @@ def main():
         res = {"ruptures_per_s": 1000.0 * B / ms_step, "ms_per_step": ms_step, "B": B, "dtypes": f"{gdt}/{fdt}",
                "products": "bf16 (high and low activation terms)" if bf16_products else
                ("f16 (bf16 operator words converted exactly in registers)" if "bf16" in (gdt, fdt) else "f16"),
-               "tuning": tuning, "kernel": elastic_kernel(op.get_tuning()["gemm_cfg"]),
+               "tuning": tuning, "kernel": elastic_kernel(op.get_tuning()["gemm_cfg"], B, bf16_products),
                "gemm_cfg": effective_tile(op.get_tuning()["gemm_cfg"], B, gdt == "bf16" and not bf16_products),
                "kernel_ms": kmean,
                "kernel_ms_min": float(np.min(kern_ms)),

@@ -22,6 +22,9 @@ constexpr int kMaxWgPerCu = 4;
 constexpr int kMaxSplits = 64;
 
 inline uint64_t round_up(uint64_t v, uint64_t a) { return (v + a - 1) / a * a; }
+// Rupture stride of the workspace regions in a call of B ruptures (the regions are sized for
+// max_batch): a few ruptures on a large plan stay dense.
+inline int batch_stride(int B) { return (B + 7) / 8 * 8; }
 inline int next_pow2(int v) {
   int p = 1;
   while (p < v) p <<= 1;
@@ -782,11 +785,15 @@ static s2w_status forward_half(s2w_plan* p, const float* s, int32_t B, float* y,
   const float* sG = (const float*)(p->op + L.sg);
   const uint4* Fq = (const uint4*)(p->op + L.fq);
   const float* sF = (const float*)(p->op + L.sf);
-  const int bp = h.bp;
+  const int bp = batch_stride(B);
   const int ncb = (2 * B + 15) / 16;
   int cfg = p->tune.gemm_cfg;
   // default tiles from sweeps on the Cascadia-sized share: with converted bfloat16 words the
   // real-column tiles lose their edge (the conversions already load the vector ALUs)
+  // up to 16 ruptures the operator streams through registers instead, and, unless the mid-chain packs
+  // or captures, the field goes through the workspace as [l][g][b]: the 64-byte runs of 8 ruptures
+  // in [g][l][b] cost the elastic product 0.7 of 3.4 ms (963 x 18,880 x 256 steps, bf16)
+  const bool stream_g = cfg < 0 && gemm_gs_fits(h.hterms_g, B);
   if (cfg < 0) cfg = h.kt_g == 3 ? (B <= 64 ? 16 : 24) : (B <= 64 ? 12 : 18);
   // acoustic GEMM: fgemm_lds 2 takes the eight-wave kernel on full activation fragments, 3 the
   // eight-wave kernel on real-column fragments (with either the mid-chain leaves complex64),
@@ -798,6 +805,8 @@ static s2w_status forward_half(s2w_plan* p, const float* s, int32_t B, float* y,
   const bool bf16_act = h.kt_f == 1;
   const bool fstaged = bf16_act && gemm_f2_supported(h.noq, B) && (fl == 4 || (fl == 1 && B <= 64));
   const bool wide_re = fl != 2;
+  const bool fscale = h.kt_f != 1;
+  const bool flat = stream_g && B <= 16 && fscale && fl == 1 && !disp && (int64_t)g.ngrid * bp <= (1 << 24);
   const int zt = fstaged ? gemm_f2_col_tiles(B) : ((g.nobs + 63) / 64) * gemm_fw_col_tiles(h.hterms_f, B, wide_re);
   int splits = p->tune.fgemm_splits;
   if (splits <= 0) splits = std::max(1, std::min(h.splits_max, 2048 / std::max(1, g.M * zt)));
@@ -815,16 +824,20 @@ static s2w_status forward_half(s2w_plan* p, const float* s, int32_t B, float* y,
   e = mark(p->ev_begin, st);
   if (e == hipSuccess) {
     const int nwg = p->ncu * p->tune.fused_wg_per_cu;
-    e = launch_gemm_g(h.kt_g, h.hterms_g, cfg, Gq, sG, Bop, sig_down, (float*)U, nwg, g.ngrid, g.M, h.nks, ncb, B, bp,
-                      st);
+    e = stream_g ? launch_gemm_gs(h.kt_g, h.hterms_g, Gq, sG, Bop, sig_down, U, flat ? bp : (int64_t)g.M * bp,
+                                  flat ? (int64_t)g.ngrid * bp : bp, g.ngrid, g.M, h.nks, B, bp, p->ncu, st)
+                 : launch_gemm_g(h.kt_g, h.hterms_g, cfg, Gq, sG, Bop, sig_down, (float*)U, nwg, g.ngrid, g.M, h.nks,
+                                 ncb, B, bp, st);
   }
   if (e == hipSuccess) e = mark(p->ev_end, st);
   if (e != hipSuccess) return hip_fail(p, e, "forward: elastic matrix-core stage");
-  const bool fscale = h.kt_f != 1;
   // float16 acoustic operands: the column scales come from maxima the mid-chain keeps as it writes
   int groups = 0;
-  e = mid_chain(p, U, sF, B, bp, false, fstaged, st, fscale ? part : nullptr,
-                       part_floats(p), &groups, disp);
+  if (flat)
+    e = g.M == 256 ? launch_mid_flat256(U, sF, B, bp, false, g, st, part, part_floats(p), &groups)
+                   : launch_mid_flat(U, sF, B, bp, false, g, st, part, part_floats(p), &groups);
+  else
+    e = mid_chain(p, U, sF, B, bp, false, fstaged, st, fscale ? part : nullptr, part_floats(p), &groups, disp);
   if (e != hipSuccess) return hip_fail(p, e, "forward: mid-chain");
   if (fscale) {
     e = launch_col_scale_final(part, groups, g.M, B, bp, tau_up, tau_down, st);
@@ -832,6 +845,10 @@ static s2w_status forward_half(s2w_plan* p, const float* s, int32_t B, float* y,
   }
   if (fstaged) {
     e = launch_gemm_f2(Fq, (const uint2*)U, part, g.ngrid, h.ngq, g.M, h.noq, B, bp, splits, st);
+  } else if (flat) {
+    splits = std::min(splits, h.ngq / 16);
+    e = launch_gemm_fs(h.kt_f, (const uint32_t*)Fq, U, tau_up, part, g.ngrid, h.ngq, g.M, h.noq, g.nobs, B, bp, splits,
+                       st);
   } else {
     splits = std::min(splits, h.ngq / 16);
     e = launch_gemm_fw(h.kt_f, h.hterms_f, (const uint32_t*)Fq, U, fscale ? tau_up : nullptr, part, g.ngrid, h.ngq,
@@ -874,7 +891,7 @@ static s2w_status forward_b32(s2w_plan* p, const float* s, int32_t B, float* y, 
   float2* S = (float2*)(p->ws + L.s32);
   float2* U = (float2*)(p->ws + L.u32);
   float* part = (float*)(p->ws + L.part32);
-  const int bp = f.bp;
+  const int bp = batch_stride(B);
   // S[l][j][b]
   hipError_t e = rfft_batch(s, B, g.nsub, f.nsk, S, bp, g, st);
   if (e != hipSuccess) return hip_fail(p, e, "forward: source transform");
@@ -913,7 +930,7 @@ static s2w_status adjoint_b32(s2w_plan* p, const float* r, int32_t B, float* gs,
   float2* R = (float2*)(p->ws + L.s32);
   float2* W = (float2*)(p->ws + L.u32);
   float* part = (float*)(p->ws + L.part32);
-  const int bp = f.bp;
+  const int bp = batch_stride(B);
   // R[l][o][b]
   hipError_t e = rfft_batch(r, B, g.nobs, f.nok, R, bp, g, st);
   if (e != hipSuccess) return hip_fail(p, e, "adjoint: residual transform");
@@ -962,7 +979,7 @@ static s2w_status adjoint_half(s2w_plan* p, const float* r, int32_t B, float* gs
   const float* sG = (const float*)(p->op + L.sg);
   const uint32_t* Fq = (const uint32_t*)(p->op + L.fq);
   const float* sF = (const float*)(p->op + L.sf);
-  const int bp = h.bp;
+  const int bp = batch_stride(B);
   const bool sf16 = h.kt_f != 1, sg16 = h.kt_g != 1;  // f16 activation terms with column scales
   hipError_t e = rfft_batch(r, B, g.nobs, g.nobs, R, bp, g, st);
   if (e == hipSuccess && sf16) e = launch_act_scale(R, g.M, g.nobs, g.nobs, B, bp, sig_up, sig_down, st);
@@ -1461,7 +1478,7 @@ s2w_status s2w_bltt_apply(s2w_bltt* p, const float* x, int32_t B, float* y, void
   if (!dg.ok) return bfail(p, S2W_EHIP, "apply: cannot select device %d", p->device);
   hipStream_t st = (hipStream_t)stream;
   const Geometry& g = p->geo;
-  const int nrow = p->desc.nrow, ncol = p->desc.ncol, bp = p->bp;
+  const int nrow = p->desc.nrow, ncol = p->desc.ncol, bp = batch_stride(B);
   const float2* Fs = (const float2*)(p->op + p->o_fs);
   float2* S = (float2*)(p->ws + p->o_s);
   float* part = (float*)(p->ws + p->o_part);
@@ -1501,7 +1518,7 @@ s2w_status s2w_bltt_adjoint(s2w_bltt* p, const float* y, int32_t B, float* x, vo
   if (!dg.ok) return bfail(p, S2W_EHIP, "adjoint: cannot select device %d", p->device);
   hipStream_t st = (hipStream_t)stream;
   const Geometry& g = p->geo;
-  const int nrow = p->desc.nrow, ncol = p->desc.ncol, bp = p->bp;
+  const int nrow = p->desc.nrow, ncol = p->desc.ncol, bp = batch_stride(B);
   const float2* Fs = (const float2*)(p->op + p->o_fs);
   float2* R = (float2*)(p->ws + p->o_s);
   float* part = (float*)(p->ws + p->o_part);

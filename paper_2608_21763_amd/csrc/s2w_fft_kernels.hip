@@ -476,7 +476,9 @@ __device__ __forceinline__ void store_v(float2* dst, float2 v, float f) {
 // With cmax, the grid is a multiple of the rupture blocks per row (nbb), so a workgroup always
 // works on the same block of ruptures; it keeps the largest |Re|, |Im| of every (slot, rupture)
 // it writes and leaves them in cmax[blockIdx / nbb][l][b] (b < bp; zero for b >= B).
-template <int PACK, int R, bool DISP, int MODE>
+// FLAT (few ruptures, bp 8 or 16): U is [l][g][b] and a unit 16 consecutive values of g * bp + b, so that
+// 8 ruptures fill a unit with two grid rows; every workgroup keeps its ruptures and leaves maxima.
+template <int PACK, int R, bool DISP, int MODE, bool FLAT = false>
 __global__ __launch_bounds__(16 * R) void k_mid_batch256(float2* __restrict__ U, const float* __restrict__ sF,
                                                          int ngrid, int B, int bp, int nt, float mscale,
                                                          float* __restrict__ cmax, DispOut disp) {
@@ -492,8 +494,10 @@ __global__ __launch_bounds__(16 * R) void k_mid_batch256(float2* __restrict__ U,
   float2 twA[15], twR[16];
   passA_twiddles(tw.c, tid & 15, twA);
   real_twiddles(tw.r, tid & 15, twR);
-  const int nbb = (B + R - 1) / R;
-  const int units = ngrid * nbb;  // the launcher checks that this fits an int
+  const int nbb = FLAT ? 1 : (B + R - 1) / R;
+  // the launcher checks that this fits an int
+  const int rows = ngrid * bp;  // FLAT
+  const int units = FLAT ? (rows + R - 1) / R : ngrid * nbb;
   float2 pre[16];
   float fs[16];
   float cmx[16];
@@ -502,14 +506,17 @@ __global__ __launch_bounds__(16 * R) void k_mid_batch256(float2* __restrict__ U,
   // loads are unconditional (ruptures past B read rupture B - 1 and are zeroed), so that the
   // gather has no lane branches
   auto fetch = [&](int u) {
-    const int g = u / nbb;
-    const int b = (u % nbb) * R + r;
-    const float2* src = U + (int64_t)g * M * bp + (b < B ? b : B - 1);
+    const int fr = FLAT ? min(u * R + r, rows - 1) : 0;
+    const int g = FLAT ? fr / bp : u / nbb;
+    const int b = FLAT ? fr - g * bp : (u % nbb) * R + r;
+    const bool ok = b < B && (!FLAT || u * R + r < rows);
+    const float2* src = FLAT ? U : U + (int64_t)g * M * bp + (b < B ? b : B - 1);
 #pragma unroll
     for (int k = 0; k < 16; ++k) {
       const int l = lq + 16 * k;
-      const float2 v = src[(int64_t)l * bp];
-      pre[k] = b < B ? v : make_float2(0.f, 0.f);
+      // FLAT: scalar base per k, 32-bit lane offset
+      const float2 v = FLAT ? (src + (int64_t)k * 16 * rows)[(uint32_t)(lq * rows + fr)] : src[(int64_t)l * bp];
+      pre[k] = ok ? v : make_float2(0.f, 0.f);
       fs[k] = sF ? sF[(int64_t)g * M + l] : 1.f;
     }
   };
@@ -529,19 +536,27 @@ __global__ __launch_bounds__(16 * R) void k_mid_batch256(float2* __restrict__ U,
     const DispRows dr{disp.base + (int64_t)g * disp.grid_stride + (int64_t)b0 * disp.row_stride, disp.row_stride,
                       B - b0, disp.scale};
     mid256<MODE>(X, T, R, nt, mscale, tw, twA, twR, LD, LD, DISP ? &dr : nullptr, dtab);
-    float2* dst = U + (int64_t)g * M * bp + b;
-    if (b < B) {
+    float2* dst = FLAT ? U : U + (int64_t)g * M * bp + b;
+    if (FLAT ? u * R + r < rows && r % bp < B : b < B) {
 #pragma unroll
       for (int k = 0; k < 16; ++k) {
         const int l = lq + 16 * k;
         const float2 v = T[r * LD + l];
-        store_v<PACK>(dst + (int64_t)l * bp, v, f[k]);
-        if (cmax) cmx[k] = fmaxf(cmx[k], fmaxf(fabsf(v.x * f[k]), fabsf(v.y * f[k])));
+        store_v<PACK>(FLAT ? dst + (int64_t)k * 16 * rows + (uint32_t)(lq * rows + u * R + r) : dst + (int64_t)l * bp, v,
+                      f[k]);
+        if (FLAT || cmax) cmx[k] = fmaxf(cmx[k], fmaxf(fabsf(v.x * f[k]), fabsf(v.y * f[k])));
       }
     }
     __syncthreads();
   }
-  if (cmax) {
+  if constexpr (FLAT) {
+    float* o = cmax + (int64_t)blockIdx.x * M * bp + r;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      const float m = bp == 8 ? fmaxf(cmx[k], __shfl_xor(cmx[k], 8, 64)) : cmx[k];
+      if (r < bp) o[(int64_t)(lq + 16 * k) * bp] = m;  // zero for b >= B
+    }
+  } else if (cmax) {
     const int b = (int)(blockIdx.x % nbb) * R + r;
     if (b < bp) {
       float* o = cmax + (int64_t)(blockIdx.x / nbb) * M * bp + b;
@@ -781,6 +796,27 @@ hipError_t launch_mid_batch256(float2* U, const float* sF, int B, int bp, bool a
   }
 #undef S2W_MID256
 #undef S2W_MID256K
+  return hipGetLastError();
+}
+
+hipError_t launch_mid_flat256(float2* U, const float* sF, int B, int bp, bool adjoint, const Geometry& g,
+                              hipStream_t st, float* cmax, int64_t cmax_floats, int* cmax_groups) {
+  if (g.M != 256 || (bp != 8 && bp != 16) || B < 1 || B > bp || g.nt > 256 || !cmax ||
+      (int64_t)g.ngrid * bp > (1 << 24))
+    return hipErrorInvalidValue;
+  const int mode = g.diff ? (adjoint ? MID_BACKWARD_T : MID_BACKWARD) : MID_NONE;
+  const float mscale = (float)(1.0 / ((double)g.L * (g.diff ? (double)g.dt : 1.0)));
+  const int64_t units = ((int64_t)g.ngrid * bp + 15) / 16;
+  const int64_t nblk = std::min<int64_t>(std::min<int64_t>(units, 256 * 4), cmax_floats / ((int64_t)g.M * bp));
+  if (nblk < 1) return hipErrorInvalidValue;
+  *cmax_groups = (int)nblk;
+#define S2W_FLAT(M_)                                                                                               \
+  hipLaunchKernelGGL((k_mid_batch256<0, 16, false, M_, true>), dim3((unsigned)nblk), dim3(256), 0, st, U, sF, g.ngrid, \
+                     B, bp, g.nt, mscale, cmax, DispOut{})
+  if (mode == MID_BACKWARD) S2W_FLAT(MID_BACKWARD);
+  else if (mode == MID_BACKWARD_T) S2W_FLAT(MID_BACKWARD_T);
+  else S2W_FLAT(MID_NONE);
+#undef S2W_FLAT
   return hipGetLastError();
 }
 

@@ -108,6 +108,15 @@ hipError_t launch_prep_act_re(int ht, int hterms, const float2* S, float* sig_up
 hipError_t launch_gemm_g(int ht, int hterms, int cfg, const uint4* Gq, const float* sG, const uint4* Bop,
                          const float* sig_down, float* U, int nwg, int ngrid, int M, int nks, int ncb, int B, int bp,
                          hipStream_t st);
+// The same products for a few ruptures, operator fragments straight into registers (same bits): elastic
+// from k_prep_act's fragments where the slot's fit in LDS (B <= 16) into U + g*u_g + l*u_l + b, acoustic
+// with float16 products (ht 2 or 3, up given, B <= 16) from V[l][g][b].
+bool gemm_gs_fits(int hterms, int B);
+hipError_t launch_gemm_gs(int ht, int hterms, const uint4* Gq, const float* sG, const uint4* Bop, const float* sig_down,
+                          float2* U, int64_t u_g, int64_t u_l, int ngrid, int M, int nks, int B, int bp, int ncu,
+                          hipStream_t st);
+hipError_t launch_gemm_fs(int ht, const uint32_t* Fq, const float2* V, const float* up, float* part, int ngrid, int ngq,
+                          int M, int noq, int nobs, int B, int bp, int splits, hipStream_t st);
 // LDS-staged acoustic GEMM (packed bfloat16 activation): supported observer paddings and the
 // number of rupture tiles it launches for a batch of B.
 inline bool gemm_f2_supported(int noq, int B) {
@@ -143,6 +152,11 @@ hipError_t launch_mid_batch256(float2* U, const float* sF, int B, int bp, bool a
 hipError_t launch_mid_units(float2* U, const float* sF, int B, int bp, bool adjoint, bool pack_bf16,
                             const Geometry& g, hipStream_t st, float* cmax, int64_t cmax_floats, int* cmax_groups,
                             const DispOut* disp);
+// The same on U[l][g][b] with bp 8 or 16, maxima always (no packing, no displacement).
+hipError_t launch_mid_flat256(float2* U, const float* sF, int B, int bp, bool adjoint, const Geometry& g,
+                              hipStream_t st, float* cmax, int64_t cmax_floats, int* cmax_groups);
+hipError_t launch_mid_flat(float2* U, const float* sF, int B, int bp, bool adjoint, const Geometry& g, hipStream_t st,
+                           float* cmax, int64_t cmax_floats, int* cmax_groups);
 // Power-of-two column scales from partial maxima part[s][l][b], s < splits (columns b >= B get 1).
 hipError_t launch_col_scale_final(const float* part, int splits, int M, int B, int bp, float* tau_up, float* tau_down,
                                   hipStream_t st);

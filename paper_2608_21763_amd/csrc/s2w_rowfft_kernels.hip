@@ -329,6 +329,9 @@ __global__ __launch_bounds__(256, 2) void k_irfft_units(const IrfftArgs p) {
 // LDS transforms it replaced spent a barrier and two LDS passes per radix-4 stage.  240 x 9,001 grid
 // rows x 500 steps (M = 512), 64 ruptures: 9.1 -> 1.3 ms (3.6 TB/s); 9,440 rows x 100 steps (M = 128),
 // 33 ruptures with snapshots: 0.58 -> 0.29 ms.
+//
+// FLAT (few ruptures, bp 8 or 16): U is [l][g][b] and a unit GA x 16 consecutive values of g * bp + b, so
+// that 8 ruptures fill a unit; every workgroup keeps its ruptures and leaves maxima.
 struct MidArgs {
   float2* U;
   const float* sF;
@@ -346,12 +349,14 @@ __device__ __forceinline__ uint32_t mid_bf16x2(float a, float b) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, mid_b2));
 }
 
-template <int M, bool PACK, bool DISP, bool CMAX>
+template <int M, bool PACK, bool DISP, bool CMAX, bool FLAT = false>
 __global__ __launch_bounds__(256, 2) void k_mid_units(const MidArgs p) {
   using F = RowFft<M>;
-  constexpr int LOGM = ilog2c(M), Q = F::GA * M / 16, NS = (F::GA * M + 255) / 256;
+  // NG: grid rows of a unit, at most
+  constexpr int LOGM = ilog2c(M), Q = F::GA * M / 16, NG = FLAT ? F::ROWS / 8 : F::GA, NS = (NG * M + 255) / 256;
+  static_assert(!FLAT || (CMAX && !PACK && !DISP), "flat units");
   __shared__ float2 X[F::ROWS * F::LD];
-  __shared__ float fsl[F::GA * M];
+  __shared__ float fsl[NG * M];
   __shared__ short dtab[DISP ? 512 : 1];
   const int tid = threadIdx.x;
   if (DISP) disp_fill_cols(p.disp, p.nt, dtab);  // ordered by the first unit's barrier
@@ -369,12 +374,19 @@ __global__ __launch_bounds__(256, 2) void k_mid_units(const MidArgs p) {
 #pragma unroll
     for (int k = 0; k < Q; ++k) cmx[k] = 0.f;
   }
+  const int rows = p.ngrid * p.bp;  // FLAT
   // loads are unconditional: rows and ruptures past the end read the last one and are zeroed
   auto fetch = [&](int u) {
-    const int g0 = (u / p.nbb) * F::GA, b = (u % p.nbb) * 16 + r;
+    const int g0 = FLAT ? u * F::ROWS / p.bp : (u / p.nbb) * F::GA, b = (u % p.nbb) * 16 + r;
 #pragma unroll
     for (int k = 0; k < Q; ++k) {
       const int q = lq + 16 * k, l = q & (M - 1), g = g0 + (q >> LOGM);
+      if (FLAT) {  // scalar base per k, 32-bit lane offset
+        const int fr = u * F::ROWS + (q >> LOGM) * 16 + r;
+        const float2 v = (p.U + (int64_t)((16 * k) & (M - 1)) * rows)[(uint32_t)(lq * rows + min(fr, rows - 1))];
+        pre[k] = fr < rows && r % p.bp < p.B ? v : make_float2(0.f, 0.f);
+        continue;
+      }
       const int gc = F::GA == 1 || g < p.ngrid ? g : p.ngrid - 1;
       const float2 v = p.U[((int64_t)gc * M + l) * p.bp + (b < p.B ? b : p.B - 1)];
       pre[k] = b < p.B && (F::GA == 1 || g < p.ngrid) ? v : make_float2(0.f, 0.f);
@@ -382,7 +394,7 @@ __global__ __launch_bounds__(256, 2) void k_mid_units(const MidArgs p) {
 #pragma unroll
     for (int k = 0; k < NS; ++k) {
       const int q = tid + 256 * k, g = g0 + (q >> LOGM);
-      fs[k] = p.sF && q < F::GA * M && g < p.ngrid ? p.sF[(int64_t)g0 * M + q] : 1.f;
+      fs[k] = p.sF && q < NG * M && g < p.ngrid ? p.sF[(int64_t)g0 * M + q] : 1.f;
     }
   };
   constexpr bool AHEAD = M < 512;
@@ -398,7 +410,7 @@ __global__ __launch_bounds__(256, 2) void k_mid_units(const MidArgs p) {
     }
 #pragma unroll
     for (int k = 0; k < NS; ++k)
-      if (tid + 256 * k < F::GA * M) fsl[tid + 256 * k] = fs[k];
+      if (tid + 256 * k < NG * M) fsl[tid + 256 * k] = fs[k];
     __syncthreads();
     if (AHEAD && u + (int)gridDim.x < p.units) fetch(u + gridDim.x);
     {
@@ -442,16 +454,17 @@ __global__ __launch_bounds__(256, 2) void k_mid_units(const MidArgs p) {
     wave_sync();
     row_forward<M>(Xr, c, tw, v);
     __syncthreads();
-    const int b = b0 + r;
+    const int b = FLAT ? r % p.bp : b0 + r;
     if (b < p.B) {
 #pragma unroll
       for (int k = 0; k < Q; ++k) {
         const int q = lq + 16 * k, l = q & (M - 1), g2 = q >> LOGM;
-        if (F::GA > 1 && g0 + g2 >= p.ngrid) continue;
-        const float f = fsl[q];
+        const int rr = g2 * 16 + r, fr = u * F::ROWS + rr;  // FLAT
+        if (FLAT ? fr >= rows : (F::GA > 1 && g0 + g2 >= p.ngrid)) continue;
+        const float f = fsl[FLAT ? rr / p.bp * M + l : q];
         const float2 x = X[(g2 * 16 + r) * F::LD + l];
         const float2 y = make_float2(x.x * f, x.y * f);
-        float2* dst = p.U + ((int64_t)(g0 + g2) * M + l) * p.bp + b;
+        float2* dst = FLAT ? (p.U + (int64_t)((16 * k) & (M - 1)) * rows) + (uint32_t)(lq * rows + fr) : p.U + ((int64_t)(g0 + g2) * M + l) * p.bp + b;
         if (PACK) {
           const uint32_t h = mid_bf16x2(y.x, y.y);
           const uint32_t lo = mid_bf16x2(y.x - __uint_as_float(h << 16), y.y - __uint_as_float(h & 0xffff0000u));
@@ -464,7 +477,18 @@ __global__ __launch_bounds__(256, 2) void k_mid_units(const MidArgs p) {
     }
     __syncthreads();  // the next unit refills X
   }
-  if (CMAX) {
+  if (FLAT) {
+    float* o = p.cmax + (int64_t)blockIdx.x * M * p.bp + r;
+    constexpr int QM = M / 16;
+#pragma unroll
+    for (int k = 0; k < QM; ++k) {
+      float m = cmx[k];
+#pragma unroll
+      for (int g2 = 1; g2 < F::GA; ++g2) m = fmaxf(m, cmx[k + QM * g2]);
+      if (p.bp == 8) m = fmaxf(m, __shfl_xor(m, 8, 64));
+      if (r < p.bp) o[(int64_t)(lq + 16 * k) * p.bp] = m;  // zero for b >= B
+    }
+  } else if (CMAX) {
     const int b = (int)(blockIdx.x % p.nbb) * 16 + r;
     if (b < p.bp) {
       float* o = p.cmax + (int64_t)(blockIdx.x / p.nbb) * M * p.bp + b;
@@ -688,6 +712,33 @@ hipError_t launch_mid_units(float2* U, const float* sF, int B, int bp, bool adjo
   S2W_BY_M_BATCH(g.M, S2W_CALL)
 #undef S2W_CALL
 #undef S2W_MID
+  return hipGetLastError();
+}
+
+hipError_t launch_mid_flat(float2* U, const float* sF, int B, int bp, bool adjoint, const Geometry& g, hipStream_t st,
+                           float* cmax, int64_t cmax_floats, int* cmax_groups) {
+  if ((bp != 8 && bp != 16) || B < 1 || B > bp || g.nt > g.M || !cmax || (int64_t)g.ngrid * bp > (1 << 24))
+    return hipErrorInvalidValue;
+  const int rows = 16 * rows_ga(g.M);
+  MidArgs a{};
+  a.U = U;
+  a.sF = sF;
+  a.ngrid = g.ngrid;
+  a.B = B;
+  a.bp = bp;
+  a.nt = g.nt;
+  a.mode = g.diff ? (adjoint ? MID_BACKWARD_T : MID_BACKWARD) : MID_NONE;
+  a.mscale = (float)(1.0 / ((double)g.L * (g.diff ? (double)g.dt : 1.0)));
+  a.cmax = cmax;
+  a.nbb = 1;
+  a.units = (int)(((int64_t)g.ngrid * bp + rows - 1) / rows);
+  const int64_t nblk = std::min<int64_t>(std::min<int64_t>(a.units, 256 * 4), cmax_floats / ((int64_t)g.M * bp));
+  if (nblk < 1) return hipErrorInvalidValue;
+  *cmax_groups = (int)nblk;
+#define S2W_CALL(M_) \
+  hipLaunchKernelGGL((k_mid_units<M_, false, false, true, true>), dim3((unsigned)nblk), dim3(256), 0, st, a)
+  S2W_BY_M_BATCH(g.M, S2W_CALL)
+#undef S2W_CALL
   return hipGetLastError();
 }
 
