@@ -231,10 +231,10 @@ typedef struct s2w_tuning {
                                 same results bit for bit), 4 LDS-staged kernel on packed bfloat16
                                 activations where its tile fits (else, and for float16 products, as 3) */
   int32_t gemm32_cfg;        /* batched float32 GEMMs over grid rows (forward elastic, adjoint acoustic): tile,
-                                -1 automatic, 1..4 = rows x ruptures 64 x 128, 128 x 32, 256 x 8, 64 x 64 */
+                                -1 automatic (64 or 256 rows by a multiple of 8 ruptures, from the
+                                sizes), 1..4 = rows x ruptures 64 x 128, 128 x 32, 256 x 8, 64 x 64 */
   int32_t gemm32_cfg_k;      /* batched float32 forward acoustic GEMM (reduces over grid rows): tile, same
-                                values (automatic: 256 x 8 for B <= 8, 64 x 64 up to B = 64, 64 x 128
-                                beyond) */
+                                values */
   int32_t gemm32_splits;     /* batched float32 acoustic GEMM: grid-row splits (1..16) */
   int32_t adj32_splits;      /* batched adjoint (float32 and half stores), transposed elastic GEMM: grid-row
                                 splits (1..8; half stores may clamp to what the partial region holds) */
@@ -245,8 +245,7 @@ typedef struct s2w_tuning {
   int32_t hadj_tile_g;       /* half-precision adjoint, transposed elastic GEMM tile: same values */
   int32_t mid_rupts;         /* batched mid-chain (Nt = 256): ruptures per work unit, 16 or 32 */
   int32_t adj32_cfg;         /* batched float32 adjoint, transposed elastic GEMM (reduces over grid rows):
-                                tile, values as gemm32_cfg (automatic: 256 x 8 for B <= 8, 128 x 32 up
-                                to B = 64, 64 x 128 beyond) */
+                                tile, values as gemm32_cfg */
 } s2w_tuning;
 
 s2w_status s2w_set_tuning(s2w_plan* plan, const s2w_tuning* t);

@@ -35,14 +35,16 @@ def candidates(op, adjoint: bool = False) -> list[dict]:
         if op.g_dtype != "f32":
             return [{"hadj_tile_f": a, "hadj_tile_g": b} for a, b in itertools.product((3, 4, 6, 7, 8), repeat=2)]
         if op.plan_layout() == "batched":
-            return [{"adj32_cfg": a} for a in (1, 2, 3, 4)]
+            return [{"adj32_cfg": a} for a in (-1, 1, 2, 3, 4)]
         return [{"fused_rows": r, "fused_wg_per_cu": w} for r in (4, 8) for w in (1, 2)]
     if op.g_dtype != "f32":
         # the automatic choice first: only it streams the operator for a few ruptures
         return [{"gemm_cfg": -1, "fgemm_lds": 1}] + \
             [{"gemm_cfg": g, "fgemm_lds": f} for g in (4, 10, 12, 16, 17, 18, 24) for f in (3, 4, 2)]
     if op.plan_layout() == "batched":
-        return [{"gemm32_cfg": a, "gemm32_cfg_k": b} for a, b in itertools.product((1, 2, 3, 4), repeat=2)]
+        # the automatic choices have tiles of every width, the settings four shapes
+        return [{"gemm32_cfg": -1, "gemm32_cfg_k": -1}] + \
+            [{"gemm32_cfg": a, "gemm32_cfg_k": b} for a, b in itertools.product((1, 2, 3, 4), repeat=2)]
     return [{"fused_rows": r, "fused_wg_per_cu": w} for r in (4, 8) for w in (1, 2)]
 
 

@@ -860,17 +860,14 @@ static s2w_status forward_half(s2w_plan* p, const float* s, int32_t B, float* y,
   return S2W_OK;
 }
 
-// Default tile of the batched float32 GEMMs for a batch of B (rows x ruptures: 0 = 64 x 128,
-// 1 = 128 x 32, 2 = 256 x 8, 3 = 64 x 64), from a sweep on the Cascadia-sized share: the
-// products over all grid rows favour tall tiles, the grid-row reductions (few output rows)
-// wide ones once the batch fills them.
-static int b32_cfg(const s2w_plan* p, int B, bool few_rows) {
-  if (few_rows) {
-    if (p->tune.gemm32_cfg_k >= 0) return p->tune.gemm32_cfg_k;
-    return B <= 8 ? 2 : (B <= 64 ? 3 : 0);
-  }
-  if (p->tune.gemm32_cfg >= 0) return p->tune.gemm32_cfg;
-  return B <= 8 ? 2 : 1;
+// Tile of a batched float32 product: the caller's choice, else by its rows and the batch.
+static int b32_cfg(int tuned, int nrows, int B) { return tuned >= 0 ? tuned : cgemm32_pick(nrows, B); }
+
+// Tile that sets the number of grid-row ranges of a reduction where the caller has chosen none: by the
+// batch alone, so that the grouping of the sums does not move with the rules of cgemm32_pick.
+static int b32_split_cfg(int tuned, int B, bool observers) {
+  if (tuned >= 0) return tuned;
+  return B <= 8 ? 2 : (B <= 64 ? (observers ? 3 : 1) : 0);
 }
 
 static int b32_splits(int tuned, int maxs, int M, int nrows, int B, int cfg) {
@@ -896,10 +893,10 @@ static s2w_status forward_b32(s2w_plan* p, const float* s, int32_t B, float* y, 
   hipError_t e = rfft_batch(s, B, g.nsub, f.nsk, S, bp, g, st);
   if (e != hipSuccess) return hip_fail(p, e, "forward: source transform");
   // U[g][l][b] = sum_j Gs[g][l][j] S[l][j][b]
-  const int cg = b32_cfg(p, B, false);
+  const int cg = b32_cfg(p->tune.gemm32_cfg, g.ngrid, B);
   e = mark(p->ev_begin, st);
   if (e == hipSuccess)
-    e = launch_cgemm32(cg, false, false, Gs, (int64_t)g.M * f.nsk, 1, f.nsk, g.ngrid, g.ngrid, f.nsk, f.nsk, S, bp,
+    e = launch_cgemm32(cg, false, Gs, (int64_t)g.M * f.nsk, 1, f.nsk, g.ngrid, g.ngrid, f.nsk, f.nsk, S, bp,
                        (int64_t)f.nsk * bp, f.nsk, B, bp, (float*)U, 2 * (int64_t)g.M * bp, 2 * (int64_t)bp, 0, g.M, 1,
                        st);
   if (e == hipSuccess) e = mark(p->ev_end, st);
@@ -907,10 +904,11 @@ static s2w_status forward_b32(s2w_plan* p, const float* s, int32_t B, float* y, 
   e = mid_chain(p, U, nullptr, B, bp, false, false, st, nullptr, 0, nullptr, disp);
   if (e != hipSuccess) return hip_fail(p, e, "forward: mid-chain");
   // part[split][l][o][n] = sum_{g in split} Fs[l][o][g] V[g][l][b]
-  const int cf = b32_cfg(p, B, true);
-  const int sf = b32_splits(p->tune.gemm32_splits, f.splits_f_max, g.M, g.nobs, B, cf);
+  const int cf = b32_cfg(p->tune.gemm32_cfg_k, g.nobs, B);
+  const int sf = b32_splits(p->tune.gemm32_splits, f.splits_f_max, g.M, g.nobs, B,
+                            b32_split_cfg(p->tune.gemm32_cfg_k, B, true));
   const int64_t prow = 2 * (int64_t)bp;
-  e = launch_cgemm32(cf, false, false, Fs, f.ngk, 1, (int64_t)f.nok * f.ngk, g.nobs, f.nok, f.ngk, f.ngk, U,
+  e = launch_cgemm32(cf, false, Fs, f.ngk, 1, (int64_t)f.nok * f.ngk, g.nobs, f.nok, f.ngk, f.ngk, U,
                      (int64_t)g.M * bp, bp, g.ngrid, B, bp, part, prow, (int64_t)f.nok * prow,
                      (int64_t)g.M * f.nok * prow, g.M, sf, st);
   if (e != hipSuccess) return hip_fail(p, e, "forward: acoustic matrix-core stage");
@@ -935,22 +933,21 @@ static s2w_status adjoint_b32(s2w_plan* p, const float* r, int32_t B, float* gs,
   hipError_t e = rfft_batch(r, B, g.nobs, f.nok, R, bp, g, st);
   if (e != hipSuccess) return hip_fail(p, e, "adjoint: residual transform");
   // W[g][l][b] = sum_o conj(Fs[l][o][g]) R[l][o][b]
-  const int c1 = b32_cfg(p, B, false);
-  e = launch_cgemm32(c1, true, true, Fs, 1, f.ngk, (int64_t)f.nok * f.ngk, g.ngrid, f.ngk, f.nok, f.nok, R, bp,
+  const int c1 = b32_cfg(p->tune.gemm32_cfg, g.ngrid, B);
+  e = launch_cgemm32(c1, true, Fs, 1, f.ngk, (int64_t)f.nok * f.ngk, g.ngrid, f.ngk, f.nok, f.nok, R, bp,
                      (int64_t)f.nok * bp, f.nok, B, bp, (float*)W, 2 * (int64_t)g.M * bp, 2 * (int64_t)bp, 0, g.M, 1,
                      st);
   if (e != hipSuccess) return hip_fail(p, e, "adjoint: acoustic matrix-core stage");
   e = mid_chain(p, W, nullptr, B, bp, true, false, st, nullptr, 0, nullptr, nullptr);
   if (e != hipSuccess) return hip_fail(p, e, "adjoint: mid-chain");
   // part[split][l][j][n] = sum_{g in split} conj(Gs[g][l][j]) W'[g][l][b]
-  // its own tile: by default 128 x 32 tiles from B = 9 to 64 (the subfault rows are many more
-  // than the forward reduction's observer rows)
-  const int c3 = p->tune.adj32_cfg >= 0 ? p->tune.adj32_cfg : (B <= 8 ? 2 : (B <= 64 ? 1 : 0));
-  const int sa = b32_splits(p->tune.adj32_splits, f.splits_a_max, g.M, g.nsub, B, c3);
+  const int c3 = b32_cfg(p->tune.adj32_cfg, g.nsub, B);
+  const int sa = b32_splits(p->tune.adj32_splits, f.splits_a_max, g.M, g.nsub, B,
+                            b32_split_cfg(p->tune.adj32_cfg, B, false));
   const int64_t prow = 2 * (int64_t)bp;
   e = mark(p->ev_begin, st);
   if (e == hipSuccess)
-    e = launch_cgemm32(c3, true, true, Gs, 1, (int64_t)g.M * f.nsk, f.nsk, g.nsub, f.nsk, g.ngrid,
+    e = launch_cgemm32(c3, true, Gs, 1, (int64_t)g.M * f.nsk, f.nsk, g.nsub, f.nsk, g.ngrid,
                        (g.ngrid + 7) / 8 * 8, W, (int64_t)g.M * bp, bp, g.ngrid, B, bp, part, prow,
                        (int64_t)f.nsk * prow, (int64_t)g.M * f.nsk * prow, g.M, sa, st);
   if (e == hipSuccess) e = mark(p->ev_end, st);
@@ -1337,11 +1334,6 @@ int bltt_splits(int M, int rows) {
   return (int)std::max<int64_t>(1, std::min<int64_t>(8, 2048 / std::max<int64_t>(1, tiles)));
 }
 
-int bltt_cfg(int B, bool few_rows) {
-  if (few_rows) return B <= 8 ? 2 : (B <= 64 ? 3 : 0);
-  return B <= 64 ? 2 : 1;
-}
-
 }  // namespace
 
 extern "C" {
@@ -1500,9 +1492,9 @@ s2w_status s2w_bltt_apply(s2w_bltt* p, const float* x, int32_t B, float* y, void
   if (e != hipSuccess) return bhip(p, e, "apply: input transform");
   // part[split][l][r][n] = sum_{c in split} Fs[r][l][c] S[l][c][b]
   const int splits = p->splits_f;
-  const int cfg = bltt_cfg(B, splits > 1);
+  const int cfg = cgemm32_pick(nrow, B);
   const int64_t prow = 2 * (int64_t)bp;
-  e = launch_cgemm32(cfg, false, false, Fs, (int64_t)g.M * p->ncol_k, 1, p->ncol_k, nrow, nrow, p->ncol_k, p->ncol_k,
+  e = launch_cgemm32(cfg, false, Fs, (int64_t)g.M * p->ncol_k, 1, p->ncol_k, nrow, nrow, p->ncol_k, p->ncol_k,
                      S, bp, (int64_t)p->ncol_k * bp, p->ncol_k, B, bp, part, prow, (int64_t)p->nrow_k * prow,
                      (int64_t)g.M * p->nrow_k * prow, g.M, splits, st);
   if (e != hipSuccess) return bhip(p, e, "apply: matrix-core product");
@@ -1527,9 +1519,9 @@ s2w_status s2w_bltt_adjoint(s2w_bltt* p, const float* y, int32_t B, float* x, vo
   if (e != hipSuccess) return bhip(p, e, "adjoint: input transform");
   // part[split][l][c][n] = sum_{r in split} conj(Fs[r][l][c]) R[l][r][b]
   const int splits = p->splits_a;
-  const int cfg = bltt_cfg(B, splits > 1);
+  const int cfg = cgemm32_pick(ncol, B);
   const int64_t prow = 2 * (int64_t)bp;
-  e = launch_cgemm32(cfg, true, true, Fs, 1, (int64_t)g.M * p->ncol_k, p->ncol_k, ncol, p->ncol_k, nrow, p->nrow_k, R,
+  e = launch_cgemm32(cfg, true, Fs, 1, (int64_t)g.M * p->ncol_k, p->ncol_k, ncol, p->ncol_k, nrow, p->nrow_k, R,
                      bp, (int64_t)p->nrow_k * bp, p->nrow_k, B, bp, part, prow, (int64_t)p->ncol_k * prow,
                      (int64_t)g.M * p->ncol_k * prow, g.M, splits, st);
   if (e != hipSuccess) return bhip(p, e, "adjoint: matrix-core product");

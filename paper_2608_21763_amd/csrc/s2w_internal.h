@@ -174,14 +174,16 @@ hipError_t launch_gemm_t(int ht, int hterms, int shape, const uint32_t* Aq, int6
 
 // ---- batched path (matrix cores, float32 stores) ----
 // Per-slot complex GEMM out(row, b) = sum_k op(A(row, k)) X(k, b) for every slot l < M:
-//   A(row, k) at A + l*a_slot + row*a_row + k*a_k (complex; rcont: a_row == 1, else a_k == 1),
+//   op: identity with a_k == 1, or (trans) the complex conjugate with a_row == 1;
+//   A(row, k) at A + l*a_slot + row*a_row + k*a_k (complex),
 //   rows < rows_alloc readable, k < kvalid nonzero, K padded to kpad (multiple of 8);
 //   X(k, b) at X + l*x_slot + k*x_k + b, rows k < xk_alloc readable;
 //   out float index split*o_split + l*o_slot + row*o_row + (2*b + re/im), rows < nrows, b < B;
 //   K split over `splits` ranges (one partial per split).
 int cgemm32_rows(int cfg);
 int cgemm32_ruptures(int cfg);
-hipError_t launch_cgemm32(int cfg, bool rcont, bool conj, const float2* A, int64_t a_row, int64_t a_k,
+int cgemm32_pick(int nrows, int B);  // tile for a product of nrows rows and B ruptures
+hipError_t launch_cgemm32(int cfg, bool trans, const float2* A, int64_t a_row, int64_t a_k,
                           int64_t a_slot, int nrows, int rows_alloc, int kvalid, int kpad, const float2* X,
                           int64_t x_k, int64_t x_slot, int xk_alloc, int B, int bp, float* out, int64_t o_row,
                           int64_t o_slot, int64_t o_split, int M, int splits, hipStream_t st);

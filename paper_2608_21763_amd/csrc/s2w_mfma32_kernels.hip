@@ -68,7 +68,7 @@ struct CGemmArgs {
 // Copies of chunk c of a float32 product into one LDS stage (see k_cgemm32d).
 template <int NRT>
 __device__ __forceinline__ int c32d_xsw(int kk) {
-  return NRT >= 32 ? ((kk >> 1) & 3) * 4 : 0;
+  return NRT % 32 == 0 ? ((kk >> 1) & 3) * 4 : (NRT % 16 == 0 ? ((kk >> 1) & 1) * 4 : 0);
 }
 
 // XOR of the row-pair units of operator k row kk (row-contiguous operators, RT >= 64)
@@ -273,26 +273,71 @@ __global__ __launch_bounds__(256, 2) void k_cgemm32d(const CGemmArgs p) {
     }
 }
 
-// Tile shapes (rows x ruptures): 0: 64 x 128, 1: 128 x 32, 2: 256 x 8, 3: 64 x 64.
-int cgemm32_rows(int cfg) { return cfg == 0 ? 64 : cfg == 1 ? 128 : cfg == 2 ? 256 : 64; }
-int cgemm32_ruptures(int cfg) { return cfg == 0 ? 128 : cfg == 1 ? 32 : cfg == 2 ? 8 : 64; }
+// Tile shapes (rows x ruptures).  0..3 are the tuning's 1..4; the others are taken by cgemm32_pick
+// only: 64 rows (4..8) and 256 rows (9..15) in widths of 8 ruptures.
+struct CTile {
+  int rows, rupts;
+};
+static const CTile kCTiles[] = {{64, 128}, {128, 32}, {256, 8},  {64, 64},  {64, 8},   {64, 16},  {64, 24},  {64, 32},
+                                {64, 48},  {256, 16}, {256, 24}, {256, 32}, {256, 40}, {256, 48}, {256, 56}, {256, 64}};
+constexpr int kNumCTiles = sizeof(kCTiles) / sizeof(kCTiles[0]);
+int cgemm32_rows(int cfg) { return kCTiles[cfg].rows; }
+int cgemm32_ruptures(int cfg) { return kCTiles[cfg].rupts; }
 
-template <bool RCONT, bool CONJ>
-static void cgemm32d_dispatch(int cfg, dim3 grid, hipStream_t st, const CGemmArgs& a) {
-  switch (cfg) {
-    case 0: hipLaunchKernelGGL((k_cgemm32d<2, 8, 2, 2, 3, RCONT, CONJ>), grid, dim3(256), 0, st, a); break;
-    case 1: hipLaunchKernelGGL((k_cgemm32d<4, 2, 2, 2, 3, RCONT, CONJ>), grid, dim3(256), 0, st, a); break;
-    case 2: hipLaunchKernelGGL((k_cgemm32d<4, 1, 4, 1, 4, RCONT, CONJ>), grid, dim3(256), 0, st, a); break;
-    default: hipLaunchKernelGGL((k_cgemm32d<2, 4, 2, 2, 3, RCONT, CONJ>), grid, dim3(256), 0, st, a); break;
-  }
+// Tile of a product with nrows rows and B ruptures.  Columns past the batch and rows past the operator
+// cost as much as real ones, so the batch is cut into equal tiles of at most 64 ruptures and the
+// narrowest tile that holds them is taken, 256 rows tall (each operator row in one wavefront or two)
+// unless 64 pads so much less that its lower rate pays (64 x 64 tiles take 1.15 times as long per
+// product as 256 x 64).  963 x 9,440 x 256 slots, forward / adjoint ms per call, where 128 x 32 tiles (the
+// tuning's 2) and 256 x 8 were all there was: B = 16 6.9 / 6.7 -> 5.1 / 4.3, 24 7.0 / 6.8 -> 6.0 / 5.7,
+// 40 11.8 / 12.5 -> 8.2 / 7.9, 48 11.8 / 12.5 -> 8.8 / 8.8, 56 12.0 / 12.6 -> 10.2 / 10.7, 64 11.8 / 12.6 ->
+// 10.9 / 11.4.  64 observers (the whole call with 16 subfaults): B = 8 0.88 -> 0.74, 16 1.19 -> 0.78, 24
+// 1.38 -> 0.99, 32 1.39 -> 1.06, 48 1.74 -> 1.54.
+int cgemm32_pick(int nrows, int B) {
+  const int nct = (B + 63) / 64, w = ((B + nct - 1) / nct + 7) / 8;  // w: units of 8 ruptures
+  auto up = [](int v, int m) { return (v + m - 1) / m * m; };
+  static const int tall[] = {2, 9, 10, 11, 12, 13, 14, 15}, low[] = {4, 5, 6, 7, 8, 8, 3, 3};
+  const int lc = low[w - 1], tc = tall[w - 1];
+  // padded rows x columns over the rates of wide batches (128 x 32 between the two: 120 rows, B = 200 8.3 -> 7.3)
+  const double ct = (double)up(nrows, 256) * nct * cgemm32_ruptures(tc);
+  const double cl = 1.15 * up(nrows, 64) * nct * cgemm32_ruptures(lc);
+  const double cm = 1.07 * up(nrows, 128) * up(B, 32);
+  return cm < cl && cm < ct ? 1 : (cl < ct ? lc : tc);
 }
 
-hipError_t launch_cgemm32(int cfg, bool rcont, bool conj, const float2* A, int64_t a_row, int64_t a_k,
+template <bool TRANS>  // the conjugate transposes read the operator row-contiguous
+static void cgemm32d_dispatch(int cfg, dim3 grid, hipStream_t st, const CGemmArgs& a) {
+#define S2W_C32(ID_, MF_, NF_, WR_, WC_, NS_)                                                                    \
+  case ID_:                                                                                                      \
+    hipLaunchKernelGGL((k_cgemm32d<MF_, NF_, WR_, WC_, NS_, TRANS, TRANS>), grid, dim3(256), 0, st, a); \
+    break
+  switch (cfg) {
+    S2W_C32(0, 2, 8, 2, 2, 3);
+    S2W_C32(1, 4, 2, 2, 2, 3);
+    S2W_C32(2, 4, 1, 4, 1, 4);
+    S2W_C32(3, 2, 4, 2, 2, 3);
+    S2W_C32(4, 1, 1, 4, 1, 4);
+    S2W_C32(5, 1, 2, 4, 1, 4);
+    S2W_C32(6, 1, 3, 4, 1, 3);
+    S2W_C32(7, 2, 2, 2, 2, 3);
+    S2W_C32(8, 2, 3, 2, 2, 3);
+    S2W_C32(9, 4, 2, 4, 1, 3);
+    S2W_C32(10, 4, 3, 4, 1, 3);
+    S2W_C32(11, 8, 2, 2, 2, 3);
+    S2W_C32(12, 4, 5, 4, 1, 3);
+    S2W_C32(13, 8, 3, 2, 2, 3);
+    S2W_C32(14, 4, 7, 4, 1, 3);
+    S2W_C32(15, 8, 4, 2, 2, 3);
+  }
+#undef S2W_C32
+}
+
+hipError_t launch_cgemm32(int cfg, bool trans, const float2* A, int64_t a_row, int64_t a_k,
                           int64_t a_slot, int nrows, int rows_alloc, int kvalid, int kpad, const float2* X,
                           int64_t x_k, int64_t x_slot, int xk_alloc, int B, int bp, float* out, int64_t o_row,
                           int64_t o_slot, int64_t o_split, int M, int splits, hipStream_t st) {
-  if (cfg < 0 || cfg > 3 || (M & 7) || (bp & 1) || bp < 2 || kpad % 8 || splits < 1) return hipErrorInvalidValue;
-  if (rcont && (rows_alloc < 2 || (rows_alloc & 1))) return hipErrorInvalidValue;
+  if (cfg < 0 || cfg >= kNumCTiles || (M & 7) || (bp & 1) || bp < 2 || kpad % 8 || splits < 1) return hipErrorInvalidValue;
+  if (trans && (rows_alloc < 2 || (rows_alloc & 1))) return hipErrorInvalidValue;
   CGemmArgs a;
   a.A = A;
   a.a_row = a_row;
@@ -319,10 +364,8 @@ hipError_t launch_cgemm32(int cfg, bool rcont, bool conj, const float2* A, int64
   const int64_t blocks = (int64_t)M * a.nrt * a.nct * splits;
   if (blocks <= 0 || blocks > 0x7fffffff) return hipErrorInvalidValue;
   const dim3 grid((unsigned)blocks);
-  if (!rcont && !conj) cgemm32d_dispatch<false, false>(cfg, grid, st, a);
-  else if (!rcont && conj) cgemm32d_dispatch<false, true>(cfg, grid, st, a);
-  else if (rcont && !conj) cgemm32d_dispatch<true, false>(cfg, grid, st, a);
-  else cgemm32d_dispatch<true, true>(cfg, grid, st, a);
+  if (trans) cgemm32d_dispatch<true>(cfg, grid, st, a);
+  else cgemm32d_dispatch<false>(cfg, grid, st, a);
   return hipGetLastError();
 }
 
