@@ -1483,7 +1483,8 @@ s2w_status s2w_bltt_apply(s2w_bltt* p, const float* x, int32_t B, float* y, void
     if (e != hipSuccess) return bhip(p, e, "apply: input transform");
     e = launch_bltt_gemv(Fs, S, yh, nrow, g.M, p->ncol_k, B, p->ncu, st);
     if (e != hipSuccess) return bhip(p, e, "apply: per-bin products");
-    e = irfft_single(yh, B * nrow, y, g, st);
+    e = launch_irfft_units(yh, 1, 0, (int64_t)g.M * nrow, 1, nrow, B, nrow, nullptr, 0, y, (int64_t)nrow * g.nt, g.nt, g,
+                           1.0f / (float)g.L, st);
     if (e != hipSuccess) return bhip(p, e, "apply: output transform");
     return S2W_OK;
   }
