@@ -413,7 +413,10 @@ s2w_status s2w_plan_create(const s2w_desc* desc, int32_t device, s2w_plan** out)
     dd.ntp = (d.nt + 15) / 16 * 16;
     const int nranges = (dd.ntp / 16 + 15) / 16;
     const int slots = 2 * ncu;  // two workgroups of four waves per compute unit
-    auto tiles = [&](int rows, int rw) { return (int64_t)((rows + 64 * rw - 1) / (64 * rw)) * nranges; };
+    auto tiles = [&](int rows, int rw) {
+      const int t = direct_tile_rows(rw, rows);
+      return (int64_t)((rows + t - 1) / t) * nranges;
+    };
     dd.s_g = direct_splits(tiles(d.ngrid, 2), d.nsub, slots, 16);
     dd.s_f = direct_splits(tiles(d.nobs, 1), d.ngrid, slots, 1024);
     dd.s_fa = direct_splits(tiles(d.ngrid, 2), d.nobs, slots, 16);

@@ -19,10 +19,14 @@
 //   D (16 x 16): column li, rows 4 kq .. 4 kq + 3.
 // K order inside a block of 16 lags: in step q (0..3) lane group kq carries lag 16 kb + 4 kq + q,
 // so a lane reads its four operator values of a block as one float4 and the matching Toeplitz
-// entries x[16 d + li - 4 kq - q] from the channel's LDS copy.  Blocks are taken in pairs
-// (2m, 2m + 1), one 128-byte line of the operator row per lane row, in the order
-// 0, P-1, 1, P-2, ... so that the long early pairs and the short late ones alternate and every
-// pair's operator loads are in flight during the previous pair's products.
+// entries x[16 d + li - 4 kq - q] from the channel's LDS copy.  Lag blocks are taken in pairs
+// (m, P - 1 - m), one long and one short, so that every pair has the same number of products over
+// the next pair's operator loads.
+//
+// Bound by the float32 matrix cores (157 TFLOP/s).  240 channels x 9,440 rows x 200 steps (1.06e11
+// operations): 1.07 ms while the wait before the products was for the next pair's loads too (they sat
+// behind a condition) and neighbouring blocks were paired, 0.95 ms now; two rounds of workgroups on 512
+// slots would take 0.72.
 #include "s2w_device.h"
 #include "s2w_internal.h"
 
@@ -44,17 +48,21 @@ struct DirectArgs {
   int64_t o_s, o_r;
   int nt, ntp;      // ntp: nt rounded up to 16
   int nrt;          // row tiles (64 * RW rows each)
-  int splits;       // channel splits, one partial output each
+  int splits;       // channel splits, one partial output each (WC waves' sums added up)
   int nranges;      // ranges of 16 output blocks (Nt > 256 needs two)
 };
 
-// Workgroup: four waves, wave w owns rows r0 + 16 RW w .. + 16 RW - 1 of the tile; all waves
-// share the staged channel.  Grid: row tile x channel split x output range.
-template <int RW>
+// Workgroup: four waves in WC groups of 4 / WC; the waves of a group own 16 RW rows each and share
+// the staged channel, the groups take channels in turn.  Grid: row tile x channel split x output
+// range.  WC > 1 is for few rows (a tile of 64 would leave waves without any): the groups' sums are
+// added through LDS at the end, group by group.
+template <int RW, int WC>
 __global__ __launch_bounds__(256, 2) void k_direct(const DirectArgs p) {
-  __shared__ float xs[2][kDirectXs];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  constexpr int GT = 256 / WC, NX = 512 / GT;  // threads of a group, staged values per thread
+  __shared__ float xs_all[2][WC][kDirectXs];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int li = lane & 15, kq = lane >> 4;
+  const int group = wave / (4 / WC), gt = tid % GT;
   int q = blockIdx.x;
   const int range = q % p.nranges;
   q /= p.nranges;
@@ -64,8 +72,8 @@ __global__ __launch_bounds__(256, 2) void k_direct(const DirectArgs p) {
   const int c1 = (int)((int64_t)p.nchan * (split + 1) / p.splits);
   const int nbt = p.ntp >> 4;                 // blocks of 16 output steps
   const int nb0 = 16 * range, nb1 = min(nb0 + 16, nbt);
-  const int npairs = (nb1 + 1) >> 1;          // lag-block pairs touching the range
-  const int r0 = rt * 64 * RW + wave * 16 * RW;
+  const int npairs = (nb1 + 1) >> 1;          // pairs of lag blocks touching the range
+  const int r0 = rt * (64 * RW / WC) + (wave % (4 / WC)) * 16 * RW;
 
   // this lane's operator rows (clamped: rows past R are loaded but never written)
   const float* arow[RW];
@@ -78,94 +86,122 @@ __global__ __launch_bounds__(256, 2) void k_direct(const DirectArgs p) {
 #pragma unroll
     for (int j = 0; j < 16; ++j) acc[rb][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  for (int i = tid; i < 16; i += 256) {
-    xs[0][i] = 0.f;
-    xs[1][i] = 0.f;
-  }
-  // staged channel values: thread t holds x[t] and x[t + 256]
-  auto load_x = [&](int c, float (&v)[2]) {
+  for (int i = tid; i < 16 * 2 * WC; i += 256) xs_all[i / 16 % 2][i / 32][i % 16] = 0.f;
+  // staged channel values: thread t of a group holds x[t + GT h] (past nt the last one, stored as zero)
+  auto load_x = [&](int c, float (&v)[NX]) {
     const float* xc = p.X + (int64_t)c * p.x_c;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int t = tid + 256 * h;
-      v[h] = t < p.nt ? xc[p.rev ? p.nt - 1 - t : t] : 0.f;
+    for (int h = 0; h < NX; ++h) {
+      const int t = min(gt + GT * h, p.nt - 1);
+      v[h] = xc[p.rev ? p.nt - 1 - t : t];
     }
   };
-  auto store_x = [&](int buf, const float (&v)[2]) {
+  auto store_x = [&](int buf, const float (&v)[NX]) {
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int t = tid + 256 * h;
-      if (t < p.ntp) xs[buf][16 + t] = v[h];
+    for (int h = 0; h < NX; ++h) {
+      const int t = gt + GT * h;
+      if (t < p.ntp) xs_all[buf][group][16 + t] = t < p.nt ? v[h] : 0.f;
     }
   };
-  // pair order: 0, P-1, 1, P-2, ...
-  auto pair_of = [&](int i) { return (i & 1) ? npairs - 1 - (i >> 1) : (i >> 1); };
+  // lag blocks of pair m: m and nb1 - 1 - m (none when they meet)
+  auto lag_of = [&](int m, int h) { return h == 0 ? m : nb1 - 1 - m; };
   auto load_a = [&](int c, int m, float4 (&a)[2][RW]) {
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      const int kb = 2 * m + h;
+      const int kb = lag_of(m, h);
 #pragma unroll
       for (int rb = 0; rb < RW; ++rb)
-        a[h][rb] = kb < nbt ? *reinterpret_cast<const float4*>(arow[rb] + (int64_t)c * p.a_c + 16 * kb)
-                            : make_float4(0.f, 0.f, 0.f, 0.f);
+        a[h][rb] = *reinterpret_cast<const float4*>(arow[rb] + (int64_t)c * p.a_c + 16 * kb);
     }
   };
   auto products = [&](const float* xb, int m, const float4 (&a)[2][RW]) {
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      const int kb = 2 * m + h;
+      const int kb = lag_of(m, h);
+      if (h == 1 && kb == m) continue;
 #pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        const int nb = nb0 + j;
-        if (nb >= kb && nb < nb1) {
-          const float* t = xb + 16 + 16 * (nb - kb) + li - 4 * kq;
-          const float b0 = t[0], b1 = t[-1], b2 = t[-2], b3 = t[-3];
+      for (int jg = 0; jg < 16; jg += 4) {  // four blocks' Toeplitz entries in flight ahead of their products
+        if (nb0 + jg + 3 < kb || nb0 + jg >= nb1) continue;
+        float b[4][4];
 #pragma unroll
-          for (int rb = 0; rb < RW; ++rb) {
-            acc[rb][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[h][rb].x, b0, acc[rb][j], 0, 0, 0);
-            acc[rb][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[h][rb].y, b1, acc[rb][j], 0, 0, 0);
-            acc[rb][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[h][rb].z, b2, acc[rb][j], 0, 0, 0);
-            acc[rb][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[h][rb].w, b3, acc[rb][j], 0, 0, 0);
-          }
+        for (int i = 0; i < 4; ++i) {
+          const float* t = xb + 16 + 16 * max(nb0 + jg + i - kb, 0) + li - 4 * kq;
+#pragma unroll
+          for (int k = 0; k < 4; ++k) b[i][k] = t[-k];
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int j = jg + i, nb = nb0 + j;
+          if (nb < kb || nb >= nb1) continue;
+#pragma unroll
+          for (int rb = 0; rb < RW; ++rb)
+            acc[rb][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[h][rb].x, b[i][0], acc[rb][j], 0, 0, 0);
+#pragma unroll
+          for (int rb = 0; rb < RW; ++rb)
+            acc[rb][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[h][rb].y, b[i][1], acc[rb][j], 0, 0, 0);
+#pragma unroll
+          for (int rb = 0; rb < RW; ++rb)
+            acc[rb][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[h][rb].z, b[i][2], acc[rb][j], 0, 0, 0);
+#pragma unroll
+          for (int rb = 0; rb < RW; ++rb)
+            acc[rb][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[h][rb].w, b[i][3], acc[rb][j], 0, 0, 0);
         }
       }
     }
   };
 
   if (c0 < c1) {
-    float xv[2];
-    load_x(c0, xv);
+    float xv[NX];
+    const int nstep = (c1 - c0 + WC - 1) / WC;
+    const int cl = c1 - 1;  // a group past its last channel loads that one and adds nothing
+    load_x(min(c0 + group, cl), xv);
     store_x(0, xv);
     float4 a0[2][RW], a1[2][RW];
-    load_a(c0, pair_of(0), a0);
+    load_a(min(c0 + group, cl), 0, a0);
     __syncthreads();
-    for (int c = c0; c < c1; ++c) {
-      const int buf = (c - c0) & 1;
-      const bool more = c + 1 < c1;
-      if (more) load_x(c + 1, xv);
-      const float* xb = xs[buf];
-      // pairs two at a time, each pair's loads issued before the previous pair's products; the
-      // last load of a channel fetches the first pair of the next one
-      for (int i = 0; i < npairs; i += 2) {
-        const bool second = i + 1 < npairs;
-        if (second) load_a(c, pair_of(i + 1), a1);
-        else if (more) load_a(c + 1, pair_of(0), a1);
-        products(xb, pair_of(i), a0);
-        if (second) {
-          if (i + 2 < npairs) load_a(c, pair_of(i + 2), a0);
-          else if (more) load_a(c + 1, pair_of(0), a0);
-          products(xb, pair_of(i + 1), a1);
-        } else {
-          // odd pair count: the next channel's first pair sits in a1
-#pragma unroll
-          for (int h = 0; h < 2; ++h)
-#pragma unroll
-            for (int rb = 0; rb < RW; ++rb) a0[h][rb] = a1[h][rb];
-        }
+    int st = 0, m = 0;  // channel step and pair of the current products
+    // The next pair's operator loads go out ahead of this pair's products, always: behind a condition
+    // the wait before the products would be for them instead of for the pair's own.
+    auto turn = [&](const float4 (&cur)[2][RW], float4 (&nxt)[2][RW]) {
+      const int cc = c0 + st * WC + group;
+      const bool last = m + 1 == npairs;
+      if (m == 0) load_x(min(cc + WC, cl), xv);
+      load_a(min(last ? cc + WC : cc, cl), last ? 0 : m + 1, nxt);
+      if (WC == 1 || cc < c1) products(xs_all[st & 1][group], m, cur);
+      m = last ? 0 : m + 1;
+      if (last) {
+        store_x(++st & 1, xv);
+        __syncthreads();
       }
-      if (more) store_x(buf ^ 1, xv);
-      __syncthreads();
+    };
+    while (st < nstep) {
+      turn(a0, a1);
+      if (st == nstep) break;
+      turn(a1, a0);
     }
+  }
+  if constexpr (WC > 1) {  // the first group adds the others' sums, four output blocks at a time
+    constexpr int GW = 4 / WC;
+    __shared__ f32x4 sum[4 - GW][RW * 4][64];
+#pragma unroll
+    for (int jg = 0; jg < 16; jg += 4) {
+      if (nb0 + jg >= nb1) break;
+      __syncthreads();
+      if (group > 0)
+#pragma unroll
+        for (int rb = 0; rb < RW; ++rb)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) sum[wave - GW][rb * 4 + i][lane] = acc[rb][jg + i];
+      __syncthreads();
+      if (group == 0)
+#pragma unroll
+        for (int g = 0; g < WC - 1; ++g)
+#pragma unroll
+          for (int rb = 0; rb < RW; ++rb)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[rb][jg + i] += sum[g * GW + wave][rb * 4 + i][lane];
+    }
+    if (group > 0) return;
   }
   float* ow = p.out + (int64_t)split * p.o_s;
 #pragma unroll
@@ -182,7 +218,9 @@ __global__ __launch_bounds__(256, 2) void k_direct(const DirectArgs p) {
     }
 }
 
-int direct_rows_per_tile(int rw) { return 64 * rw; }
+// Row tile of a product with R rows: 64 rw rows, or 32 and 16 with the waves in groups by channel
+// when R fits: 16 rows, 9,440 channels, 200 steps take 321 us in 64-row tiles, 87 in 16-row ones.
+int direct_tile_rows(int rw, int R) { return R <= 16 ? 16 : R <= 32 ? 32 : 64 * rw; }
 
 hipError_t launch_direct(int rw, const float* A, int64_t a_c, int64_t a_r, int R, int nchan, const float* X,
                          int64_t x_c, bool rev, float* out, int64_t o_s, int64_t o_r, int nt, int splits,
@@ -190,6 +228,7 @@ hipError_t launch_direct(int rw, const float* A, int64_t a_c, int64_t a_r, int R
   if ((rw != 1 && rw != 2) || nt < 1 || nt > 512 || R < 1 || nchan < 1 || splits < 1 || splits > nchan ||
       (a_c & 3) || (a_r & 3) || ((uintptr_t)A & 15))
     return hipErrorInvalidValue;
+  const int rows = direct_tile_rows(rw, R);
   DirectArgs a;
   a.A = A;
   a.a_c = a_c;
@@ -204,15 +243,20 @@ hipError_t launch_direct(int rw, const float* A, int64_t a_c, int64_t a_r, int R
   a.o_r = o_r;
   a.nt = nt;
   a.ntp = (nt + 15) / 16 * 16;
-  a.nrt = (R + 64 * rw - 1) / (64 * rw);
+  a.nrt = (R + rows - 1) / rows;
   a.splits = splits;
   a.nranges = (a.ntp / 16 + 15) / 16;
   const int64_t blocks = (int64_t)a.nrt * splits * a.nranges;
   if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-  if (rw == 1)
-    hipLaunchKernelGGL((k_direct<1>), dim3((unsigned)blocks), dim3(256), 0, st, a);
+  const dim3 grid((unsigned)blocks);
+  if (rows == 16)
+    hipLaunchKernelGGL((k_direct<1, 4>), grid, dim3(256), 0, st, a);
+  else if (rows == 32)
+    hipLaunchKernelGGL((k_direct<1, 2>), grid, dim3(256), 0, st, a);
+  else if (rows == 64)
+    hipLaunchKernelGGL((k_direct<1, 1>), grid, dim3(256), 0, st, a);
   else
-    hipLaunchKernelGGL((k_direct<2>), dim3((unsigned)blocks), dim3(256), 0, st, a);
+    hipLaunchKernelGGL((k_direct<2, 1>), grid, dim3(256), 0, st, a);
   return hipGetLastError();
 }
 
@@ -222,36 +266,70 @@ hipError_t launch_direct(int rw, const float* A, int64_t a_c, int64_t a_r, int R
 // Between the two products it forms D_t of the seafloor field (forward) or, on the time-reversed
 // correlation, D_t^T (the adjoint); at the end it sums the output partials.  In the forward map
 // S is the seafloor displacement m of eq. (1), which `disp` may capture at selected steps.
+// A thread sums four consecutive steps (16-byte loads; p_s and p_r are multiples of 4, partial rows
+// whole fours).  Up to 16 partials it takes them all; the many partials of few rows are dealt to PL
+// threads and their sums added through LDS, in order.  One step per thread and all partials in one
+// chain took 42 us for 13 partials of 9,440 x 200 and 122 us for 512 of 16 x 200; now 20 and 6.
+template <int PL>
 __global__ __launch_bounds__(256) void k_direct_reduce(const float* __restrict__ part, int parts, int64_t p_s,
                                                        int64_t p_r, int R, int nt, int rev, int diff, float scale,
                                                        float* __restrict__ out, int64_t o_r, DispOut disp) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= (int64_t)R * nt) return;
-  const int r = (int)(i / nt), n = (int)(i % nt);
-  const float* pr = part + (int64_t)r * p_r;
-  const int t = rev ? nt - 1 - n : n;
-  float s = 0.f;
-  for (int q = 0; q < parts; ++q) s += pr[(int64_t)q * p_s + t];
-  if (disp.base && r < disp.rows) {
-    const int c = disp_col(disp, n);
-    if (c >= 0) disp.base[(int64_t)r * disp.row_stride + c] = s * disp.scale;
+  constexpr int IT = 256 / PL;  // fours of steps per workgroup
+  const int item = threadIdx.x % IT, pl = threadIdx.x / IT;
+  const int n4 = (nt + 3) / 4;
+  const int64_t i = (int64_t)blockIdx.x * IT + item;
+  const bool on = i < (int64_t)R * n4;
+  const int r = on ? (int)(i / n4) : 0, t0 = on ? 4 * (int)(i - (int64_t)r * n4) : 0;
+  const float* pr = part + (int64_t)r * p_r + t0;
+  const int prev = diff && t0 > 0 ? -1 : 0;  // the step before the four, for the difference
+  float s[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll 8
+  for (int q = pl; q < parts; q += PL) {
+    const float4 v = *reinterpret_cast<const float4*>(pr + (int64_t)q * p_s);
+    if (diff) s[0] += pr[(int64_t)q * p_s + prev];
+    s[1] += v.x;
+    s[2] += v.y;
+    s[3] += v.z;
+    s[4] += v.w;
   }
-  if (diff && n > 0) {
-    const int t1 = rev ? nt - n : n - 1;
-    float s1 = 0.f;
-    for (int q = 0; q < parts; ++q) s1 += pr[(int64_t)q * p_s + t1];
-    s -= s1;
+  if constexpr (PL > 1) {
+    __shared__ float sum[PL][5][IT];
+#pragma unroll
+    for (int k = 0; k < 5; ++k) sum[pl][k][item] = s[k];
+    __syncthreads();
+    if (pl > 0) return;
+    for (int g = 1; g < PL; ++g)
+#pragma unroll
+      for (int k = 0; k < 5; ++k) s[k] += sum[g][k][item];
   }
-  out[(int64_t)r * o_r + n] = s * scale;
+  if (!on) return;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int t = t0 + k, n = rev ? nt - 1 - t : t;
+    if (t >= nt) break;
+    float v = s[k + 1];
+    if (disp.base && r < disp.rows) {
+      const int c = disp_col(disp, n);
+      if (c >= 0) disp.base[(int64_t)r * disp.row_stride + c] = v * disp.scale;
+    }
+    if (diff && t > 0) v -= s[k];
+    out[(int64_t)r * o_r + n] = v * scale;
+  }
 }
 
 hipError_t launch_direct_reduce(const float* part, int parts, int64_t p_s, int64_t p_r, int R, int nt, bool rev,
                                 bool diff, float scale, float* out, int64_t o_r, hipStream_t st,
                                 const DispOut* disp) {
-  if (parts < 1 || R < 1 || nt < 1) return hipErrorInvalidValue;
-  const int64_t items = (int64_t)R * nt;
-  hipLaunchKernelGGL(k_direct_reduce, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, st, part, parts, p_s, p_r,
-                     R, nt, rev ? 1 : 0, diff ? 1 : 0, scale, out, o_r, disp ? *disp : DispOut{});
+  if (parts < 1 || R < 1 || nt < 1 || (p_s & 3) || (p_r & 3) || p_r < (nt + 3) / 4 * 4 || (rev && diff))
+    return hipErrorInvalidValue;
+  const int64_t items = (int64_t)R * ((nt + 3) / 4);
+  const DispOut d = disp ? *disp : DispOut{};
+  if (parts <= 16)
+    hipLaunchKernelGGL((k_direct_reduce<1>), dim3((unsigned)((items + 255) / 256)), dim3(256), 0, st, part, parts, p_s,
+                       p_r, R, nt, rev ? 1 : 0, diff ? 1 : 0, scale, out, o_r, d);
+  else
+    hipLaunchKernelGGL((k_direct_reduce<32>), dim3((unsigned)((items + 7) / 8)), dim3(256), 0, st, part, parts, p_s, p_r,
+                       R, nt, rev ? 1 : 0, diff ? 1 : 0, scale, out, o_r, d);
   return hipGetLastError();
 }
 

@@ -192,11 +192,12 @@ hipError_t launch_cgemm32(int cfg, bool trans, const float2* A, int64_t a_row, i
 // out[split][r][n] = sum over the split's channels c of sum_{k<=n} A(c, r, k) x_c[n - k], n < nt,
 // A(c, r, k) at A + c*a_c + r*a_r + k (16-byte aligned rows, zeros at k >= nt up to nt rounded to
 // 16), x_c[p] at X + c*x_c + (rev ? nt - 1 - p : p); rw = 1 or 2 row blocks of 16 per wave.
-int direct_rows_per_tile(int rw);
+int direct_tile_rows(int rw, int R);  // rows of a workgroup's tile in a product of R rows
 hipError_t launch_direct(int rw, const float* A, int64_t a_c, int64_t a_r, int R, int nchan, const float* X,
                          int64_t x_c, bool rev, float* out, int64_t o_s, int64_t o_r, int nt, int splits,
                          hipStream_t st);
-// out[r*o_r + n] = scale * (S(r, n) - diff * S(r, n-1)), S(r, n) = sum_q part[q*p_s + r*p_r + (rev ? nt-1-n : n)]
+// out[r*o_r + n] = scale * (S(r, n) - diff * S(r, n-1)), S(r, n) = sum_q part[q*p_s + r*p_r + (rev ? nt-1-n : n)];
+// p_s and p_r multiples of 4, no diff with rev
 hipError_t launch_direct_reduce(const float* part, int parts, int64_t p_s, int64_t p_r, int R, int nt, bool rev,
                                 bool diff, float scale, float* out, int64_t o_r, hipStream_t st,
                                 const DispOut* disp = nullptr);
