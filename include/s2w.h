@@ -193,7 +193,7 @@ s2w_status s2w_adjoint(s2w_plan* plan, const float* r, int32_t B, float* gs, voi
  * Limits: single-layout (float32) plans whose fused kernel fits the array, i.e.
  * (M*nsp + nwg*M*nop + nop*M) * 8 bytes, each term rounded up to 256, is at most
  * S2W_NOALLOC_SCRATCH_BYTES, with M = L/2 slots, nsp / nop = nsub / nobs rounded up to even,
- * nwg = compute units x fused_wg_per_cu (the Cascadia-sized share, 963 x 37,760 x 64 x 256
+ * nwg = compute units x fused_wg_per_cu (unless set, one, or two where those fit; the Cascadia-sized share, 963 x 37,760 x 64 x 256
  * at one workgroup per CU, needs 35.6 MB); larger plans, batched or half-precision plans and
  * plans whose observers need the unfused kernel get S2W_EUNSUPPORTED with the byte count in
  * s2w_last_error, before anything is enqueued.
@@ -206,8 +206,8 @@ s2w_status s2w_forward_noalloc(s2w_plan* plan, const float* s, int32_t B, float*
 
 /* Kernel-shape controls for the tuner.  Zero fields keep the library default. */
 typedef struct s2w_tuning {
-  int32_t fused_wg_per_cu;   /* single-rupture fused kernel: workgroups per compute unit (1..4) */
-  int32_t fused_rows;        /* single-rupture fused kernel: grid rows per tile (4 or 8) */
+  int32_t fused_wg_per_cu;   /* single-rupture fused kernel: workgroups per compute unit (1..4); by size unless set */
+  int32_t fused_rows;        /* single-rupture fused kernel: grid rows per tile (4 or 8); by size unless set */
   int32_t adj_cols;          /* grid-row contractions (adjoint elastic stage): columns per thread (8 or 16); until this
                               * or adj_splits is set, both are chosen from the sizes */
   int32_t adj_splits;        /* single-rupture adjoint: grid splits of the transposed elastic stage */

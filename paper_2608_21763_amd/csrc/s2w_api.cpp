@@ -119,6 +119,7 @@ struct s2w_plan {
   Layout lay;
   s2w_tuning tune;
   bool adj_set = false;          // the caller chose adj_cols or adj_splits
+  bool fused_set = false;        // the caller chose fused_wg_per_cu or fused_rows
   char* op = nullptr;
   char* ws = nullptr;
   uint64_t op_bytes = 0, ws_bytes = 0;
@@ -532,6 +533,7 @@ s2w_status s2w_set_tuning(s2w_plan* p, const s2w_tuning* t) {
     n.adj_splits = t->adj_splits;
   }
   const bool adj_set = t->adj_cols || t->adj_splits;
+  const bool fused_set = t->fused_wg_per_cu || t->fused_rows;
   if (t->gemm_cfg) {
     const int c = t->gemm_cfg;
     if (!(c == -1 || c == 4 || c == 10 || c == 12 || (c >= 16 && c <= 18) || c == 24))
@@ -584,6 +586,7 @@ s2w_status s2w_set_tuning(s2w_plan* p, const s2w_tuning* t) {
   }
   p->tune = n;
   p->adj_set = p->adj_set || adj_set;
+  p->fused_set = p->fused_set || fused_set;
   return S2W_OK;
 }
 
@@ -768,6 +771,14 @@ static hipError_t rfft_single(const float* in, int nrows, int nrows_pad, float2*
 }
 static hipError_t irfft_single(const float2* in, int nrows, float* out, const Geometry& g, hipStream_t st) {
   return launch_irfft_units(in, 1, 0, 0, g.M, 1, 1, nrows, nullptr, 0, out, 0, g.nt, g, 1.0f / (float)g.L, st);
+}
+
+// Series of nrows rows from their partial spectra [p][nop][M]; sum: nop x M slots of scratch.
+static hipError_t sum_irfft(const float2* part, int nparts, int nrows, int nop, float2* sum, float* out,
+                            const Geometry& g, hipStream_t st) {
+  if (sum_irfft_rows_fits(g.M, nparts)) return launch_sum_irfft_rows(part, nparts, nrows, nop, out, g, st);
+  hipError_t e = launch_sum_parts(part, nparts, (int64_t)nop * g.M, sum, st);
+  return e == hipSuccess ? irfft_single(sum, nrows, out, g, st) : e;
 }
 
 // Batched forward on the matrix cores (half-precision stores).
@@ -1172,15 +1183,41 @@ s2w_status s2w_forward_displacement(s2w_plan* p, const float* s, int32_t B, floa
 
 // Bytes of scratch the single-layout forward needs for its source spectrum, the fused
 // kernel's per-workgroup partial spectra and their sum (the fused kernel only).
-static uint64_t single_fused_scratch(const s2w_plan* p, uint64_t* o_part, uint64_t* o_yh) {
+static uint64_t single_fused_scratch(const s2w_plan* p, int wg_per_cu, uint64_t* o_part, uint64_t* o_yh) {
   const Geometry& g = p->geo;
   const uint64_t c8 = sizeof(float2);
-  const uint64_t nwg = (uint64_t)p->ncu * p->tune.fused_wg_per_cu;
+  const uint64_t nwg = (uint64_t)p->ncu * wg_per_cu;
   uint64_t off = round_up((uint64_t)g.M * g.nsp * c8, kAlign);
   *o_part = off;
   off = round_up(off + nwg * g.M * g.nop * c8, kAlign);
   *o_yh = off;
   return round_up(off + (uint64_t)g.nop * g.M * c8, kAlign);
+}
+
+// Workgroups and tile rows of the fused forward, unless the caller has set them.
+//   Two workgroups per CU hide each other's mid-chain where the operator rows are short next to it (and
+//   their scratch fits the call without a workspace): 30 subfaults x 37,760 rows x 4 observers x 256 slots
+//   615 -> 481 us, 120 x 20,000 x 8 822 -> 788; but 480 x 37,758 x 32 5,612 -> 5,814, and 60 x 3,000 x 4
+//   has 12 rows per CU: 98 -> 102.
+//   Tiles of 4 rows take more time per row than tiles of 8 but waste less at the end of a workgroup's
+//   range: 963 x 4,720 x 64 1,580 -> 1,477 (20 rows for 24), 60 x 30,207 x 4 662 -> 692 (60 for 64).
+struct FusedShape {
+  int wg_per_cu, nwg, rows;
+};
+static int fused_tile_rows(int ngrid, int nwg) {
+  const int r = (ngrid + nwg - 1) / nwg;
+  return (r + 3) / 4 * 4 * 100 <= (r + 7) / 8 * 8 * 93 ? 4 : 8;
+}
+static FusedShape fused_shape(const s2w_plan* p) {
+  const Geometry& g = p->geo;
+  if (p->fused_set) return {p->tune.fused_wg_per_cu, p->ncu * p->tune.fused_wg_per_cu, p->tune.fused_rows};
+  uint64_t o = 0;
+  const bool two = g.nsub <= 160 && g.ngrid >= 16 * p->ncu &&
+                   single_fused_scratch(p, 2, &o, &o) <= (uint64_t)S2W_NOALLOC_SCRATCH_BYTES;
+  FusedShape f{two ? 2 : 1, 0, 0};
+  f.rows = fused_tile_rows(g.ngrid, p->ncu * f.wg_per_cu);
+  f.nwg = std::min(p->ncu * f.wg_per_cu, (g.ngrid + f.rows - 1) / f.rows);  // no partial spectra without rows
+  return f;
 }
 
 s2w_status s2w_forward_noalloc(s2w_plan* p, const float* s, int32_t B, float* y, void* stream) {
@@ -1192,12 +1229,12 @@ s2w_status s2w_forward_noalloc(s2w_plan* p, const float* s, int32_t B, float* y,
     return fail(p, S2W_EUNSUPPORTED, "forward_noalloc: %d observers at L = %d need the unfused path", p->geo.nobs,
                 p->geo.L);
   uint64_t o_part = 0, o_yh = 0;
-  const uint64_t need = single_fused_scratch(p, &o_part, &o_yh);
+  const uint64_t need = single_fused_scratch(p, fused_shape(p).wg_per_cu, &o_part, &o_yh);
   if (need > (uint64_t)S2W_NOALLOC_SCRATCH_BYTES)
     return fail(p, S2W_EUNSUPPORTED,
                 "forward_noalloc: needs %llu bytes of scratch (%d workgroups x %d observers x %d slots), the fixed "
                 "array holds %llu",
-                (unsigned long long)need, p->ncu * p->tune.fused_wg_per_cu, p->geo.nop, p->geo.M,
+                (unsigned long long)need, p->ncu * fused_shape(p).wg_per_cu, p->geo.nop, p->geo.M,
                 (unsigned long long)S2W_NOALLOC_SCRATCH_BYTES);
   DeviceGuard dg(p->device);
   if (!dg.ok) return fail(p, S2W_EHIP, "forward_noalloc: cannot select device %d", p->device);
@@ -1218,7 +1255,7 @@ static s2w_status forward_single(s2w_plan* p, const float* s, int32_t B, float* 
   const float2* Fh = (const float2*)(p->op + p->lay.fh);
   const bool fused = fused_forward_opt(g) <= 32;
   if (!fused && !Vh) return fail(p, S2W_EUNSUPPORTED, "forward: the unfused path needs the bound workspace");
-  const int nwg = p->ncu * p->tune.fused_wg_per_cu;
+  const FusedShape fs = fused_shape(p);
   int cols = p->adj_set ? p->tune.adj_cols : 0, splits = p->tune.adj_splits;
   rows_contract_shape(g.nop, g.ngrid, kMaxSplits, g, &cols, &splits);
   for (int b = 0; b < B; ++b) {
@@ -1234,19 +1271,17 @@ static s2w_status forward_single(s2w_plan* p, const float* s, int32_t B, float* 
     }
     e = mark(p->ev_begin, st);
     if (fused) {
-      if (e == hipSuccess) e = launch_fused_forward(Gh, Fh, Sh, part, nwg, p->tune.fused_rows, g, st, db);
+      if (e == hipSuccess) e = launch_fused_forward(Gh, Fh, Sh, part, fs.nwg, fs.rows, g, st, db);
       if (e == hipSuccess) e = mark(p->ev_end, st);
-      nparts = nwg;
+      nparts = fs.nwg;
     } else {
-      if (e == hipSuccess) e = launch_forward_rows(Gh, Sh, Vh, nwg, g, st, db);
+      if (e == hipSuccess) e = launch_forward_rows(Gh, Sh, Vh, p->ncu * p->tune.fused_wg_per_cu, g, st, db);
       if (e == hipSuccess) e = mark(p->ev_end, st);
       if (e == hipSuccess) e = launch_rows_acoustic(Fh, Vh, part, cols, splits, g, st);
       nparts = splits;
     }
     if (e != hipSuccess) return hip_fail(p, e, "forward: contraction");
-    e = launch_sum_parts(part, nparts, (int64_t)g.nop * g.M, yh, st);
-    if (e != hipSuccess) return hip_fail(p, e, "forward: partial sum");
-    e = irfft_single(yh, g.nobs, yb, g, st);
+    e = sum_irfft(part, nparts, g.nobs, g.nop, yh, yb, g, st);
     if (e != hipSuccess) return hip_fail(p, e, "forward: output transform");
   }
   return S2W_OK;
@@ -1268,7 +1303,9 @@ s2w_status s2w_adjoint(s2w_plan* p, const float* r, int32_t B, float* gs, void* 
   float2* Wp = (float2*)(p->ws + p->lay.wp);
   float2* part = (float2*)(p->ws + p->lay.part2);
   float2* gsh = (float2*)(p->ws + p->lay.gsh);
-  const int nwg = p->ncu * p->tune.fused_wg_per_cu;
+  // two workgroups per CU unless the caller has set it (16 x 9,440 x 4 x 256, whole call: 173 -> 150 us)
+  const int nwg = p->ncu * (p->fused_set ? p->tune.fused_wg_per_cu : 2);
+  const int rows = p->fused_set ? p->tune.fused_rows : fused_tile_rows(g.ngrid, nwg);
   int cols = p->adj_set ? p->tune.adj_cols : 0, splits = p->tune.adj_splits;
   rows_contract_shape(g.nsp, g.ngrid, kMaxSplits, g, &cols, &splits);
   for (int b = 0; b < B; ++b) {
@@ -1276,15 +1313,13 @@ s2w_status s2w_adjoint(s2w_plan* p, const float* r, int32_t B, float* gs, void* 
     float* gb = gs + (int64_t)b * g.nsub * g.nt;
     hipError_t e = rfft_single(rb, g.nobs, g.nop, Rh, g, st);
     if (e != hipSuccess) return hip_fail(p, e, "adjoint: residual transform");
-    e = launch_adjoint_rows(Fh, Rh, Wp, nwg, p->tune.fused_rows, g, st);
+    e = launch_adjoint_rows(Fh, Rh, Wp, nwg, rows, g, st);
     if (e != hipSuccess) return hip_fail(p, e, "adjoint: acoustic stage");
     e = mark(p->ev_begin, st);
     if (e == hipSuccess) e = launch_adjoint_elastic(Gh, Wp, part, cols, splits, g, st);
     if (e == hipSuccess) e = mark(p->ev_end, st);
     if (e != hipSuccess) return hip_fail(p, e, "adjoint: elastic stage");
-    e = launch_sum_parts(part, splits, (int64_t)g.nsp * g.M, gsh, st);
-    if (e != hipSuccess) return hip_fail(p, e, "adjoint: partial sum");
-    e = irfft_single(gsh, g.nsub, gb, g, st);
+    e = sum_irfft(part, splits, g.nsub, g.nsp, gsh, gb, g, st);
     if (e != hipSuccess) return hip_fail(p, e, "adjoint: output transform");
   }
   return S2W_OK;

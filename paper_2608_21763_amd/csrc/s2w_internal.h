@@ -52,6 +52,11 @@ hipError_t launch_rfft_units(const float* in, int64_t in_a, int64_t in_b, int na
 hipError_t launch_irfft_units(const float2* part, int splits, int64_t p_s, int64_t pa, int64_t pb, int64_t pl, int na,
                               int nb, const float* tau, int64_t tau_l, float* out, int64_t oa, int64_t ob,
                               const Geometry& g, float scale, hipStream_t st);
+// out[o*nt + n] = IFFT(sum_p part[p][o][.])[n] / L, o < nrows, part[p][o][l] with nop rows per partial, in
+// one launch where the partials are few.
+bool sum_irfft_rows_fits(int M, int nparts);
+hipError_t launch_sum_irfft_rows(const float2* part, int nparts, int nrows, int nop, float* out, const Geometry& g,
+                                 hipStream_t st);
 // Half-precision setup: spectra of in[row][col][nt] as scaled half words (ht: 1 = bf16, 2 = f16) with
 // one power-of-two scale per (grid row, slot), down[(row0 + row)*M + l].  Elastic: row-block-major
 // words (((l*nrb + g/16)*(ncp/16) + c/16)*16 + g%16)*16 + c%16; else word c*w_col + l*w_slot + g,

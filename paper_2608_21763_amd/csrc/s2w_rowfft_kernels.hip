@@ -316,6 +316,56 @@ __global__ __launch_bounds__(256, 2) void k_irfft_units(const IrfftArgs p) {
   }
 }
 
+// Fixed-order sum of partial spectra and inverse real FFT of one row per workgroup,
+//   out[o * nt + n] = scale * IFFT(sum_p part[p][o][.])[n],  n < nt  (part rows of M slots, nop per partial).
+// QL threads share a pair of slots: thread q sums partials q, q + QL, ... (eight loads in flight; past
+// the end the last one, not added), then the QL sums are added in order through LDS.
+//
+// Bound by latency: the sum and the transform are a few microseconds each whatever their bytes.  128
+// partials of 4 x 32 slots 5.5 + 4.2 us as two launches, 4.7 as one; 256 of 32 x 256 (17 MB) 16 -> 11; 64 of
+// 60 x 256 10 + 7 -> 7.6.
+template <int M>
+__global__ __launch_bounds__(1024) void k_sum_irfft_rows(const v4f* __restrict__ part, int nparts, int64_t p_s,
+                                                         float* __restrict__ out, int nt, float scale) {
+  using F = RowFft<M>;
+  constexpr int I = M / 2, QL = 1024 / I;
+  __shared__ v4f sh[QL][I];
+  __shared__ float2 X[F::LD];
+  const int tid = threadIdx.x, it = tid % I, q = tid / I;
+  const v4f* src = part + (int64_t)blockIdx.x * I + it;
+  v4f s = v4f{0.f, 0.f, 0.f, 0.f};
+  for (int p = q; p < nparts; p += 8 * QL) {
+    v4f a[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) a[u] = src[(int64_t)min(p + u * QL, nparts - 1) * p_s];
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (p + u * QL < nparts) s += a[u];
+  }
+  sh[q][it] = s;
+  __syncthreads();
+  if (q == 0) {
+    for (int k = 1; k < QL; ++k) s += sh[k][it];
+    X[2 * it] = make_float2(s.x, s.y);
+    X[2 * it + 1] = make_float2(s.z, s.w);
+  }
+  __syncthreads();
+  if (tid >= F::TPR) return;
+  RowTw<M> tw;
+  tw.init(tid, nullptr);
+  float2 z[F::CB][F::N2];
+  row_inverse<M>(X, tid, tw, z);
+  float* dst = out + (int64_t)blockIdx.x * nt;
+#pragma unroll
+  for (int i = 0; i < F::CB; ++i)
+#pragma unroll
+    for (int k2 = 0; k2 < F::N2 / 2; ++k2) {
+      const int m0 = 2 * (tid + F::TPR * i + F::N1 * k2);
+      if (m0 < nt) dst[m0] = z[i][k2].x * scale;
+      if (m0 + 1 < nt) dst[m0 + 1] = z[i][k2].y * scale;
+    }
+}
+
 // Batched mid-chain round trip on U[g][l][b] (complex, b < bp), in place: for GA grid rows and 16
 // ruptures, inverse FFT -> truncate -> D_t -> zero-pad -> FFT (Alg. 1 line 3; Alg. 2 steps 4-5 and
 // 1-2), times the store's scale sF[g][l], written as complex64 (PACK = 0) or as bfloat16 high and
@@ -662,6 +712,28 @@ hipError_t launch_irfft_units(const float2* part, int splits, int64_t p_s, int64
   else                                                                            \
     hipLaunchKernelGGL((k_irfft_units<M_, false>), grid, dim3(256), 0, st, a)
   S2W_BY_M(g.M, S2W_CALL)
+#undef S2W_CALL
+  return hipGetLastError();
+}
+
+// Up to four rounds of eight loads per thread (512 partials of 4 x 256 slots, eight rounds, stay with the sum
+// of their own over more workgroups); a row of 512 slots does not fit the registers of 1,024 threads.
+bool sum_irfft_rows_fits(int M, int nparts) { return M <= 256 && (int64_t)nparts * M <= 65536; }
+
+hipError_t launch_sum_irfft_rows(const float2* part, int nparts, int nrows, int nop, float* out, const Geometry& g,
+                                 hipStream_t st) {
+  if (nparts < 1 || nrows < 1 || nrows > nop || g.nt < 1 || g.nt > g.M || !sum_irfft_rows_fits(g.M, nparts))
+    return hipErrorInvalidValue;
+#define S2W_CALL(M_)                                                                                             \
+  hipLaunchKernelGGL((k_sum_irfft_rows<M_>), dim3((unsigned)nrows), dim3(1024), 0, st, (const v4f*)part, nparts, \
+                     (int64_t)nop * (M_ / 2), out, g.nt, 1.0f / (float)g.L)
+  switch (g.M) {
+    case 16: S2W_CALL(16); break;
+    case 32: S2W_CALL(32); break;
+    case 64: S2W_CALL(64); break;
+    case 128: S2W_CALL(128); break;
+    default: S2W_CALL(256); break;
+  }
 #undef S2W_CALL
   return hipGetLastError();
 }
