@@ -918,7 +918,8 @@ static s2w_status forward_b32(s2w_plan* p, const float* s, int32_t B, float* y, 
   e = mid_chain(p, U, nullptr, B, bp, false, false, st, nullptr, 0, nullptr, disp);
   if (e != hipSuccess) return hip_fail(p, e, "forward: mid-chain");
   // part[split][l][o][n] = sum_{g in split} Fs[l][o][g] V[g][l][b]
-  const int cf = b32_cfg(p->tune.gemm32_cfg_k, g.nobs, B);
+  const int cf = p->tune.gemm32_cfg_k < 0 && cgemm32_few_rows(g.nobs) ? kCFewRows
+                                                                          : b32_cfg(p->tune.gemm32_cfg_k, g.nobs, B);
   const int sf = b32_splits(p->tune.gemm32_splits, f.splits_f_max, g.M, g.nobs, B,
                             b32_split_cfg(p->tune.gemm32_cfg_k, B, true));
   const int64_t prow = 2 * (int64_t)bp;

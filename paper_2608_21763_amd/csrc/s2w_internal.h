@@ -188,6 +188,8 @@ hipError_t launch_gemm_t(int ht, int hterms, int shape, const uint32_t* Aq, int6
 int cgemm32_rows(int cfg);
 int cgemm32_ruptures(int cfg);
 int cgemm32_pick(int nrows, int B);  // tile for a product of nrows rows and B ruptures
+constexpr int kCFewRows = 100;       // cfg of the register kernel for few rows (not transposed)
+bool cgemm32_few_rows(int nrows);
 hipError_t launch_cgemm32(int cfg, bool trans, const float2* A, int64_t a_row, int64_t a_k,
                           int64_t a_slot, int nrows, int rows_alloc, int kvalid, int kpad, const float2* X,
                           int64_t x_k, int64_t x_slot, int xk_alloc, int B, int bp, float* out, int64_t o_row,

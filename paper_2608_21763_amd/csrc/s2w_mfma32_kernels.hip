@@ -273,6 +273,101 @@ __global__ __launch_bounds__(256, 2) void k_cgemm32d(const CGemmArgs p) {
     }
 }
 
+// Products of at most 32 rows, k-contiguous operator: the same fragments, products and order as
+// k_cgemm32d, but straight from global memory into registers, so that one wavefront owns 16 MF rows and
+// 8 NF ruptures of a slot and range (16 observers fill a quarter of a tile of 64 rows, which keeps four
+// wavefronts and barriers busy).  Three chunks of 8 complex k load under the products of a fourth.
+//
+// Bound by HBM latency and the activations' bytes.  16 observers x 4,000 grid rows x 256 slots, 64 ruptures
+// (524 + 131 MB): 385 us in 64 x 64 tiles, 298 with one chunk in flight, 230 with three.  32 observers x 9,440
+// grid rows, 64 ruptures: 760 -> 447 us.
+template <int MF, int NF>
+__global__ __launch_bounds__(64) void k_cgemm32s(const CGemmArgs p) {
+  const int lane = threadIdx.x;
+  const int ci = lane & 1, n = lane & 15, kq = lane >> 4;
+  const int x = blockIdx.x & 7;
+  int q = blockIdx.x >> 3;
+  const int split = q % p.splits;
+  q /= p.splits;
+  const int ct = q % p.nct, l = x + 8 * (q / p.nct);
+  const bool dc = (l == 0);
+  const int c0 = (int)((int64_t)p.nchunks * split / p.splits);
+  const int c1 = (int)((int64_t)p.nchunks * (split + 1) / p.splits);
+  const int b0 = ct * 8 * NF;
+  const float2* Al[MF];
+#pragma unroll
+  for (int a = 0; a < MF; ++a)
+    Al[a] = p.A + (int64_t)l * p.a_slot + (int64_t)min(16 * a + n, p.rows_alloc - 1) * p.a_row + 2 * kq;
+  const float2* Xl = p.X + (int64_t)l * p.x_slot;
+  int bx[NF];
+#pragma unroll
+  for (int f = 0; f < NF; ++f) bx[f] = min(b0 + 8 * f + (n >> 1), p.bp - 1);
+  f32x4 acc[MF][NF];
+#pragma unroll
+  for (int a = 0; a < MF; ++a)
+#pragma unroll
+    for (int f = 0; f < NF; ++f) acc[a][f] = f32x4{0.f, 0.f, 0.f, 0.f};
+  struct Chunk {
+    float4 a[MF];
+    float2 x[NF][2];
+  };
+  auto load = [&](int c, Chunk& r) {  // past the range the last chunk again (never used)
+    c = min(c, c1 - 1);
+#pragma unroll
+    for (int a = 0; a < MF; ++a) r.a[a] = *reinterpret_cast<const float4*>(Al[a] + 8 * c);
+    const int k = 8 * c + 2 * kq;
+    const float2* x0 = Xl + (int64_t)min(k, p.xk_alloc - 1) * p.x_k;
+    const float2* x1 = Xl + (int64_t)min(k + 1, p.xk_alloc - 1) * p.x_k;
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+      r.x[f][0] = x0[bx[f]];
+      r.x[f][1] = x1[bx[f]];
+    }
+  };
+  auto products = [&](int c, const Chunk& r) {
+    const bool k0ok = 8 * c + 2 * kq < p.kvalid, k1ok = 8 * c + 2 * kq + 1 < p.kvalid;
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+      float bv[4];
+      embed32<false>(k0ok ? r.x[f][0] : make_float2(0.f, 0.f), ci, dc, bv[0], bv[1]);
+      embed32<false>(k1ok ? r.x[f][1] : make_float2(0.f, 0.f), ci, dc, bv[2], bv[3]);
+#pragma unroll
+      for (int a = 0; a < MF; ++a) acc[a][f] = __builtin_amdgcn_mfma_f32_16x16x4f32(r.a[a].x, bv[0], acc[a][f], 0, 0, 0);
+#pragma unroll
+      for (int a = 0; a < MF; ++a) acc[a][f] = __builtin_amdgcn_mfma_f32_16x16x4f32(r.a[a].y, bv[1], acc[a][f], 0, 0, 0);
+#pragma unroll
+      for (int a = 0; a < MF; ++a) acc[a][f] = __builtin_amdgcn_mfma_f32_16x16x4f32(r.a[a].z, bv[2], acc[a][f], 0, 0, 0);
+#pragma unroll
+      for (int a = 0; a < MF; ++a) acc[a][f] = __builtin_amdgcn_mfma_f32_16x16x4f32(r.a[a].w, bv[3], acc[a][f], 0, 0, 0);
+    }
+  };
+  if (c0 < c1) {
+    constexpr int D = 4;  // chunks held: three in flight under the products of the fourth
+    Chunk r[D];
+#pragma unroll
+    for (int d = 0; d < D - 1; ++d) load(c0 + d, r[d]);
+    for (int c = c0; c < c1; c += D)
+#pragma unroll
+      for (int d = 0; d < D; ++d) {
+        load(c + d + D - 1, r[(d + D - 1) % D]);
+        if (c + d < c1) products(c + d, r[d]);
+      }
+  }
+  float* ow = p.out + (int64_t)split * p.o_split + (int64_t)l * p.o_slot;
+#pragma unroll
+  for (int a = 0; a < MF; ++a)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = 16 * a + 4 * kq + r;
+      if (row >= p.nrows) continue;
+#pragma unroll
+      for (int f = 0; f < NF; ++f) {
+        const int col = 2 * b0 + 16 * f + n;
+        if (col < p.ncols) ow[(int64_t)row * p.o_row + col] = acc[a][f][r];
+      }
+    }
+}
+
 // Tile shapes (rows x ruptures).  0..3 are the tuning's 1..4; the others are taken by cgemm32_pick
 // only: 64 rows (4..8) and 256 rows (9..15) in widths of 8 ruptures.
 struct CTile {
@@ -305,6 +400,11 @@ int cgemm32_pick(int nrows, int B) {
   return cm < cl && cm < ct ? 1 : (cl < ct ? lc : tc);
 }
 
+// The register kernel up to two fragments of rows: whole calls of 16 subfaults x 4,000 x 256, 16 / 32 / 48
+// observers, where cgemm32_pick's tiles take (8 ruptures) 264 / 274 / 306 and (64) 797 / 798 / 806 us, take
+// 244 / 272 / 326 and 642 / 683 / 892.
+bool cgemm32_few_rows(int nrows) { return nrows <= 32; }
+
 template <bool TRANS>  // the conjugate transposes read the operator row-contiguous
 static void cgemm32d_dispatch(int cfg, dim3 grid, hipStream_t st, const CGemmArgs& a) {
 #define S2W_C32(ID_, MF_, NF_, WR_, WC_, NS_)                                                                    \
@@ -332,11 +432,37 @@ static void cgemm32d_dispatch(int cfg, dim3 grid, hipStream_t st, const CGemmArg
 #undef S2W_C32
 }
 
+static hipError_t cgemm32s(CGemmArgs& a, int B, hipStream_t st) {
+  a.nrt = 1;
+  a.nct = (B + 63) / 64;
+  const int nf = ((B + a.nct - 1) / a.nct + 7) / 8;
+  const int64_t blocks = (int64_t)a.M * a.nct * a.splits;
+  if (blocks > 0x7fffffff) return hipErrorInvalidValue;
+#define S2W_FEW(NF_)                                                                                                  \
+  case NF_:                                                                                                           \
+    if (a.nrows <= 16) hipLaunchKernelGGL((k_cgemm32s<1, NF_>), dim3((unsigned)blocks), dim3(64), 0, st, a); \
+    else hipLaunchKernelGGL((k_cgemm32s<2, NF_>), dim3((unsigned)blocks), dim3(64), 0, st, a);               \
+    break
+  switch (nf) {
+    S2W_FEW(1);
+    S2W_FEW(2);
+    S2W_FEW(3);
+    S2W_FEW(4);
+    S2W_FEW(5);
+    S2W_FEW(6);
+    S2W_FEW(7);
+    S2W_FEW(8);
+  }
+#undef S2W_FEW
+  return hipGetLastError();
+}
+
 hipError_t launch_cgemm32(int cfg, bool trans, const float2* A, int64_t a_row, int64_t a_k,
                           int64_t a_slot, int nrows, int rows_alloc, int kvalid, int kpad, const float2* X,
                           int64_t x_k, int64_t x_slot, int xk_alloc, int B, int bp, float* out, int64_t o_row,
                           int64_t o_slot, int64_t o_split, int M, int splits, hipStream_t st) {
-  if (cfg < 0 || cfg >= kNumCTiles || (M & 7) || (bp & 1) || bp < 2 || kpad % 8 || splits < 1) return hipErrorInvalidValue;
+  const bool few = cfg == kCFewRows && !trans;
+  if ((!few && (cfg < 0 || cfg >= kNumCTiles)) || (M & 7) || (bp & 1) || bp < 2 || kpad % 8 || splits < 1) return hipErrorInvalidValue;
   if (trans && (rows_alloc < 2 || (rows_alloc & 1))) return hipErrorInvalidValue;
   CGemmArgs a;
   a.A = A;
@@ -358,9 +484,13 @@ hipError_t launch_cgemm32(int cfg, bool trans, const float2* A, int64_t a_row, i
   a.o_split = o_split;
   a.ncols = 2 * B;
   a.M = M;
+  a.splits = splits;
+  if (few) {
+    if (nrows < 1 || !cgemm32_few_rows(nrows) || B < 1 || (a_row & 1) || (a_slot & 1) || a_k != 1) return hipErrorInvalidValue;
+    return cgemm32s(a, B, st);
+  }
   a.nrt = (nrows + cgemm32_rows(cfg) - 1) / cgemm32_rows(cfg);
   a.nct = (B + cgemm32_ruptures(cfg) - 1) / cgemm32_ruptures(cfg);
-  a.splits = splits;
   const int64_t blocks = (int64_t)M * a.nrt * a.nct * splits;
   if (blocks <= 0 || blocks > 0x7fffffff) return hipErrorInvalidValue;
   const dim3 grid((unsigned)blocks);
