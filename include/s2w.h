@@ -233,8 +233,8 @@ typedef struct s2w_tuning {
   int32_t gemm32_cfg;        /* batched float32 GEMMs over grid rows (forward elastic, adjoint acoustic): tile,
                                 -1 automatic (64 or 256 rows by a multiple of 8 ruptures, from the
                                 sizes), 1..4 = rows x ruptures 64 x 128, 128 x 32, 256 x 8, 64 x 64 */
-  int32_t gemm32_cfg_k;      /* batched float32 forward acoustic GEMM (reduces over grid rows): tile, same values, automatic
-                                at most 32 observers take a register kernel of 16 or 32 rows instead */
+  int32_t gemm32_cfg_k;      /* batched float32 forward acoustic GEMM (reduces over grid rows): tile, same
+                                values; automatic takes a register kernel for at most 32 observers */
   int32_t gemm32_splits;     /* batched float32 acoustic GEMM: grid-row splits (1..16) */
   int32_t adj32_splits;      /* batched adjoint (float32 and half stores), transposed elastic GEMM: grid-row
                                 splits (1..8; half stores may clamp to what the partial region holds) */
