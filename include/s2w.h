@@ -193,8 +193,9 @@ s2w_status s2w_adjoint(s2w_plan* plan, const float* r, int32_t B, float* gs, voi
  * Limits: single-layout (float32) plans whose fused kernel fits the array, i.e.
  * (M*nsp + nwg*M*nop + nop*M) * 8 bytes, each term rounded up to 256, is at most
  * S2W_NOALLOC_SCRATCH_BYTES, with M = L/2 slots, nsp / nop = nsub / nobs rounded up to even,
- * nwg = compute units x fused_wg_per_cu (unless set, one, or two where those fit; the Cascadia-sized share, 963 x 37,760 x 64 x 256
- * at one workgroup per CU, needs 35.6 MB); larger plans, batched or half-precision plans and
+ * nwg = compute units x fused_wg_per_cu (automatic: one, or two where those fit; the
+ * Cascadia-sized share, 963 x 37,760 x 64 x 256 at one workgroup per CU, needs 35.6 MB); larger
+ * plans, batched or half-precision plans and
  * plans whose observers need the unfused kernel get S2W_EUNSUPPORTED with the byte count in
  * s2w_last_error, before anything is enqueued.
  * Concurrency: every call on one GPU shares that GPU's array, so calls that overlap on one
@@ -206,11 +207,11 @@ s2w_status s2w_forward_noalloc(s2w_plan* plan, const float* s, int32_t B, float*
 
 /* Kernel-shape controls for the tuner.  Zero fields keep the library default. */
 typedef struct s2w_tuning {
-  int32_t fused_wg_per_cu;   /* single-rupture fused kernel: workgroups per compute unit (1..4); by size unless set */
-  int32_t fused_rows;        /* single-rupture fused kernel: grid rows per tile (4 or 8); by size unless set */
-  int32_t adj_cols;          /* grid-row contractions (adjoint elastic stage): columns per thread (8 or 16); until this
-                              * or adj_splits is set, both are chosen from the sizes */
-  int32_t adj_splits;        /* single-rupture adjoint: grid splits of the transposed elastic stage */
+  int32_t fused_wg_per_cu;   /* single-rupture kernels: workgroups per compute unit, -1 automatic (by size), 1..4 */
+  int32_t fused_rows;        /* single-rupture kernels: grid rows per tile, -1 automatic (by size), 4 or 8 */
+  int32_t adj_cols;          /* grid-row contractions (adjoint elastic stage): columns per thread, -1 automatic (by
+                              * size), 8 or 16 */
+  int32_t adj_splits;        /* grid-row contractions: row ranges, -1 automatic (by size), 1..64 */
   int32_t batch_path_min_b;  /* reserved: ignored (the layout, fixed at plan creation, picks the path) */
   int32_t gemm_cfg;          /* batched elastic GEMM tile, 256 grid rows tall, persistent workgroups:
                                 -1 automatic (up to B = 32 the operator streams through registers, no

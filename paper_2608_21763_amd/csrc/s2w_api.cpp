@@ -118,8 +118,6 @@ struct s2w_plan {
   DirectGeo dg;
   Layout lay;
   s2w_tuning tune;
-  bool adj_set = false;          // the caller chose adj_cols or adj_splits
-  bool fused_set = false;        // the caller chose fused_wg_per_cu or fused_rows
   char* op = nullptr;
   char* ws = nullptr;
   uint64_t op_bytes = 0, ws_bytes = 0;
@@ -424,10 +422,10 @@ s2w_status s2w_plan_create(const s2w_desc* desc, int32_t device, s2w_plan** out)
     dd.s_ga = direct_splits(tiles(d.nsub, 2), d.ngrid, slots, 1024);
   }
   p->lay = make_layout(d, g, h, p->fb, p->dg, ncu);
-  p->tune.fused_wg_per_cu = 1;
-  p->tune.fused_rows = 8;
-  p->tune.adj_cols = 16;
-  p->tune.adj_splits = 16;
+  p->tune.fused_wg_per_cu = -1;
+  p->tune.fused_rows = -1;
+  p->tune.adj_cols = -1;
+  p->tune.adj_splits = -1;
   p->tune.batch_path_min_b = 0;
   p->tune.gemm_cfg = -1;
   p->tune.fgemm_splits = 0;
@@ -517,23 +515,25 @@ s2w_status s2w_set_tuning(s2w_plan* p, const s2w_tuning* t) {
   if (!p || !t) return S2W_EINVAL;
   s2w_tuning n = p->tune;
   if (t->fused_wg_per_cu) {
-    if (t->fused_wg_per_cu < 1 || t->fused_wg_per_cu > kMaxWgPerCu) return fail(p, S2W_EINVAL, "tuning: fused_wg_per_cu");
-    n.fused_wg_per_cu = t->fused_wg_per_cu;
+    const int c = t->fused_wg_per_cu;
+    if (c != -1 && (c < 1 || c > kMaxWgPerCu)) return fail(p, S2W_EINVAL, "tuning: fused_wg_per_cu");
+    n.fused_wg_per_cu = c;
   }
   if (t->fused_rows) {
-    if (t->fused_rows != 4 && t->fused_rows != 8) return fail(p, S2W_EINVAL, "tuning: fused_rows must be 4 or 8");
-    n.fused_rows = t->fused_rows;
+    const int c = t->fused_rows;
+    if (c != -1 && c != 4 && c != 8) return fail(p, S2W_EINVAL, "tuning: fused_rows must be -1, 4 or 8");
+    n.fused_rows = c;
   }
   if (t->adj_cols) {
-    if (t->adj_cols != 8 && t->adj_cols != 16) return fail(p, S2W_EINVAL, "tuning: adj_cols must be 8 or 16");
-    n.adj_cols = t->adj_cols;
+    const int c = t->adj_cols;
+    if (c != -1 && c != 8 && c != 16) return fail(p, S2W_EINVAL, "tuning: adj_cols must be -1, 8 or 16");
+    n.adj_cols = c;
   }
   if (t->adj_splits) {
-    if (t->adj_splits < 1 || t->adj_splits > kMaxSplits) return fail(p, S2W_EINVAL, "tuning: adj_splits");
-    n.adj_splits = t->adj_splits;
+    const int c = t->adj_splits;
+    if (c != -1 && (c < 1 || c > kMaxSplits)) return fail(p, S2W_EINVAL, "tuning: adj_splits");
+    n.adj_splits = c;
   }
-  const bool adj_set = t->adj_cols || t->adj_splits;
-  const bool fused_set = t->fused_wg_per_cu || t->fused_rows;
   if (t->gemm_cfg) {
     const int c = t->gemm_cfg;
     if (!(c == -1 || c == 4 || c == 10 || c == 12 || (c >= 16 && c <= 18) || c == 24))
@@ -585,8 +585,6 @@ s2w_status s2w_set_tuning(s2w_plan* p, const s2w_tuning* t) {
     n.hadj_tile_g = t->hadj_tile_g < 0 ? -1 : t->hadj_tile_g - 1;
   }
   p->tune = n;
-  p->adj_set = p->adj_set || adj_set;
-  p->fused_set = p->fused_set || fused_set;
   return S2W_OK;
 }
 
@@ -754,6 +752,11 @@ static hipError_t sum_and_irfft(const float* part, int splits, int noq, int nrow
                             tau, bp, out, g.nt, (int64_t)nrows * g.nt, g, 1.0f / (float)g.L, st);
 }
 
+// Workgroups per compute unit: the caller's choice, else the kernel's own.
+static int wg_per_cu(const s2w_plan* p, int automatic) {
+  return p->tune.fused_wg_per_cu > 0 ? p->tune.fused_wg_per_cu : automatic;
+}
+
 // Mid-chain of the batched paths; *groups (when given) is the count of partial maxima left in cmax.
 static hipError_t mid_chain(s2w_plan* p, float2* U, const float* scale, int B, int bp, bool adjoint, bool pack_bf16,
                             hipStream_t st, float* cmax, int64_t cmax_floats, int* groups, const DispOut* disp) {
@@ -837,7 +840,7 @@ static s2w_status forward_half(s2w_plan* p, const float* s, int32_t B, float* y,
   if (e != hipSuccess) return hip_fail(p, e, "forward: source transform");
   e = mark(p->ev_begin, st);
   if (e == hipSuccess) {
-    const int nwg = p->ncu * p->tune.fused_wg_per_cu;
+    const int nwg = p->ncu * wg_per_cu(p, 1);
     e = stream_g ? launch_gemm_gs(h.kt_g, h.hterms_g, Gq, sG, Bop, sig_down, U, flat ? bp : (int64_t)g.M * bp,
                                   flat ? (int64_t)g.ngrid * bp : bp, g.ngrid, g.M, h.nks, B, bp, p->ncu, st)
                  : launch_gemm_g(h.kt_g, h.hterms_g, cfg, Gq, sG, Bop, sig_down, (float*)U, nwg, g.ngrid, g.M, h.nks,
@@ -1195,29 +1198,31 @@ static uint64_t single_fused_scratch(const s2w_plan* p, int wg_per_cu, uint64_t*
   return round_up(off + (uint64_t)g.nop * g.M * c8, kAlign);
 }
 
-// Workgroups and tile rows of the fused forward, unless the caller has set them.
-//   Two workgroups per CU hide each other's mid-chain where the operator rows are short next to it (and
-//   their scratch fits the call without a workspace): 30 subfaults x 37,760 rows x 4 observers x 256 slots
-//   615 -> 481 us, 120 x 20,000 x 8 822 -> 788; but 480 x 37,758 x 32 5,612 -> 5,814, and 60 x 3,000 x 4
-//   has 12 rows per CU: 98 -> 102.
+// Workgroups and tile rows of the fused forward, each by size unless the caller has set it.
+//   Two workgroups per CU hide each other's mid-chain where the operator rows are short next to it:
+//   30 subfaults x 37,760 rows x 4 observers x 256 slots 615 -> 481 us, 120 x 20,000 x 8 822 -> 788; but
+//   480 x 37,758 x 32 5,612 -> 5,814, and 60 x 3,000 x 4 has 12 rows per CU: 98 -> 102.  Not where their
+//   scratch is too much for s2w_forward_noalloc, which gives the same bits and serves those plans with one.
 //   Tiles of 4 rows take more time per row than tiles of 8 but waste less at the end of a workgroup's
 //   range: 963 x 4,720 x 64 1,580 -> 1,477 (20 rows for 24), 60 x 30,207 x 4 662 -> 692 (60 for 64).
 struct FusedShape {
   int wg_per_cu, nwg, rows;
 };
-static int fused_tile_rows(int ngrid, int nwg) {
-  const int r = (ngrid + nwg - 1) / nwg;
+static int fused_tile_rows(const s2w_plan* p, int nwg) {
+  if (p->tune.fused_rows > 0) return p->tune.fused_rows;
+  const int r = (p->geo.ngrid + nwg - 1) / nwg;
   return (r + 3) / 4 * 4 * 100 <= (r + 7) / 8 * 8 * 93 ? 4 : 8;
 }
 static FusedShape fused_shape(const s2w_plan* p) {
   const Geometry& g = p->geo;
-  if (p->fused_set) return {p->tune.fused_wg_per_cu, p->ncu * p->tune.fused_wg_per_cu, p->tune.fused_rows};
   uint64_t o = 0;
   const bool two = g.nsub <= 160 && g.ngrid >= 16 * p->ncu &&
                    single_fused_scratch(p, 2, &o, &o) <= (uint64_t)S2W_NOALLOC_SCRATCH_BYTES;
-  FusedShape f{two ? 2 : 1, 0, 0};
-  f.rows = fused_tile_rows(g.ngrid, p->ncu * f.wg_per_cu);
-  f.nwg = std::min(p->ncu * f.wg_per_cu, (g.ngrid + f.rows - 1) / f.rows);  // no partial spectra without rows
+  FusedShape f{wg_per_cu(p, two ? 2 : 1), 0, 0};
+  f.nwg = p->ncu * f.wg_per_cu;
+  f.rows = fused_tile_rows(p, f.nwg);
+  // no partial spectra without rows
+  if (p->tune.fused_wg_per_cu < 0) f.nwg = std::min(f.nwg, (g.ngrid + f.rows - 1) / f.rows);
   return f;
 }
 
@@ -1257,7 +1262,7 @@ static s2w_status forward_single(s2w_plan* p, const float* s, int32_t B, float* 
   const bool fused = fused_forward_opt(g) <= 32;
   if (!fused && !Vh) return fail(p, S2W_EUNSUPPORTED, "forward: the unfused path needs the bound workspace");
   const FusedShape fs = fused_shape(p);
-  int cols = p->adj_set ? p->tune.adj_cols : 0, splits = p->tune.adj_splits;
+  int cols = p->tune.adj_cols, splits = p->tune.adj_splits;
   rows_contract_shape(g.nop, g.ngrid, kMaxSplits, g, &cols, &splits);
   for (int b = 0; b < B; ++b) {
     const float* sb = s + (int64_t)b * g.nsub * g.nt;
@@ -1276,7 +1281,7 @@ static s2w_status forward_single(s2w_plan* p, const float* s, int32_t B, float* 
       if (e == hipSuccess) e = mark(p->ev_end, st);
       nparts = fs.nwg;
     } else {
-      if (e == hipSuccess) e = launch_forward_rows(Gh, Sh, Vh, p->ncu * p->tune.fused_wg_per_cu, g, st, db);
+      if (e == hipSuccess) e = launch_forward_rows(Gh, Sh, Vh, p->ncu * wg_per_cu(p, 1), g, st, db);
       if (e == hipSuccess) e = mark(p->ev_end, st);
       if (e == hipSuccess) e = launch_rows_acoustic(Fh, Vh, part, cols, splits, g, st);
       nparts = splits;
@@ -1304,10 +1309,12 @@ s2w_status s2w_adjoint(s2w_plan* p, const float* r, int32_t B, float* gs, void* 
   float2* Wp = (float2*)(p->ws + p->lay.wp);
   float2* part = (float2*)(p->ws + p->lay.part2);
   float2* gsh = (float2*)(p->ws + p->lay.gsh);
-  // two workgroups per CU unless the caller has set it (16 x 9,440 x 4 x 256, whole call: 173 -> 150 us)
-  const int nwg = p->ncu * (p->fused_set ? p->tune.fused_wg_per_cu : 2);
-  const int rows = p->fused_set ? p->tune.fused_rows : fused_tile_rows(g.ngrid, nwg);
-  int cols = p->adj_set ? p->tune.adj_cols : 0, splits = p->tune.adj_splits;
+  // two workgroups per CU: whole calls of 15 sizes between 4 and 963 subfaults, 300 and 37,760 rows, 16 and
+  // 512 slots take 0.85 (4 x 30,000 x 1 x 32, 201 -> 172 us) to 1.03 (16 x 1,000 x 64 x 256, 56 -> 58 us)
+  // of the time with one
+  const int nwg = p->ncu * wg_per_cu(p, 2);
+  const int rows = fused_tile_rows(p, nwg);
+  int cols = p->tune.adj_cols, splits = p->tune.adj_splits;
   rows_contract_shape(g.nsp, g.ngrid, kMaxSplits, g, &cols, &splits);
   for (int b = 0; b < B; ++b) {
     const float* rb = r + (int64_t)b * g.nobs * g.nt;

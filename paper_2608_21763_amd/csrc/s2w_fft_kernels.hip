@@ -399,19 +399,23 @@ __global__ __launch_bounds__(256) void k_rows_contract(const v4f* __restrict__ X
   }
 }
 
-// Columns per thread and row ranges where the caller has not set them (cols = 0), towards 240
+// Columns per thread and row ranges, each where the caller has not set it (negative), towards 240
 // workgroups (more ranges only add partial sums: 963 columns at 16, 32 and 64 ranges 1.52, 1.59,
 // 1.70 ms per adjoint of 4,720 rows): sixteen columns and 16 ranges where those give as many (480
 // columns 1.47 against 1.49-1.52 ms with 8, 963 columns 1.52 against 1.56), else 8 columns (240 columns
 // 0.80 against 0.96), and 4 where 8 with every range allowed still gives fewer (60 columns of 128
 // slots 0.18 against 0.21 ms).
 void rows_contract_shape(int ncp, int ngrid, int max_splits, const Geometry& g, int* cols, int* splits) {
-  if (*cols) return;
   const int CS = 256 / (g.M / 2);
   auto blocks = [&](int c) { return (ncp + c * CS - 1) / (c * CS); };
-  *cols = blocks(16) * 16 >= 240 ? 16 : (blocks(8) * max_splits >= 240 ? 8 : 4);
-  const int want = *cols == 16 ? 16 : std::max(16, (240 + blocks(*cols) - 1) / blocks(*cols));
-  *splits = std::max(1, std::min(std::min(max_splits, want), (ngrid + 3) / 4));
+  if (*cols < 0)
+    *cols = blocks(16) * (*splits < 0 ? 16 : *splits) >= 240           ? 16
+            : blocks(8) * (*splits < 0 ? max_splits : *splits) >= 240 ? 8
+                                                                      : 4;
+  if (*splits < 0) {
+    const int want = *cols == 16 ? 16 : std::max(16, (240 + blocks(*cols) - 1) / blocks(*cols));
+    *splits = std::max(1, std::min(std::min(max_splits, want), (ngrid + 3) / 4));
+  }
 }
 
 template <bool CONJ>

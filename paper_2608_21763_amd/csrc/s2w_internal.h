@@ -93,7 +93,7 @@ hipError_t launch_adjoint_rows(const float2* Fh, const float2* Rh, float2* Wp, i
 hipError_t launch_adjoint_elastic(const float2* Gh, const float2* Wp, float2* part, int cols_per_thread, int splits,
                                   const Geometry& g, hipStream_t st);
 
-// Columns per thread and row ranges of a contraction over the grid rows, where *cols is 0.
+// Columns per thread and row ranges of a contraction over the grid rows, each where it is negative.
 void rows_contract_shape(int ncp, int ngrid, int max_splits, const Geometry& g, int* cols, int* splits);
 
 // Unfused forward: stage 1 writes the per-row mid-chain output Vh[g][l]; stage 2
