@@ -36,7 +36,7 @@ def candidates(op, adjoint: bool = False) -> list[dict]:
             return [{"hadj_tile_f": a, "hadj_tile_g": b} for a, b in itertools.product((3, 4, 6, 7, 8), repeat=2)]
         if op.plan_layout() == "batched":
             return [{"adj32_cfg": a} for a in (-1, 1, 2, 3, 4)]
-        return [{"fused_rows": r, "fused_wg_per_cu": w} for r in (4, 8) for w in (1, 2)]
+        return _single()
     if op.g_dtype != "f32":
         # the automatic choice first: only it streams the operator for a few ruptures
         return [{"gemm_cfg": -1, "fgemm_lds": 1}] + \
@@ -45,7 +45,14 @@ def candidates(op, adjoint: bool = False) -> list[dict]:
         # the automatic choices have tiles of every width, the settings four shapes
         return [{"gemm32_cfg": -1, "gemm32_cfg_k": -1}] + \
             [{"gemm32_cfg": a, "gemm32_cfg_k": b} for a, b in itertools.product((1, 2, 3, 4), repeat=2)]
-    return [{"fused_rows": r, "fused_wg_per_cu": w} for r in (4, 8) for w in (1, 2)]
+    return _single()
+
+
+def _single() -> list[dict]:
+    # the automatic choice first: only it takes other shapes in the forward than in the adjoint and
+    # leaves out workgroups without rows
+    return [{"fused_rows": -1, "fused_wg_per_cu": -1}] + \
+        [{"fused_rows": r, "fused_wg_per_cu": w} for r in (4, 8) for w in (1, 2)]
 
 
 def _key(op, B: int) -> str:
