@@ -1263,7 +1263,7 @@ static s2w_status forward_single(s2w_plan* p, const float* s, int32_t B, float* 
   if (!fused && !Vh) return fail(p, S2W_EUNSUPPORTED, "forward: the unfused path needs the bound workspace");
   const FusedShape fs = fused_shape(p);
   int cols = p->tune.adj_cols, splits = p->tune.adj_splits;
-  rows_contract_shape(g.nop, g.ngrid, kMaxSplits, g, &cols, &splits);
+  rows_contract_shape(g.nop, g.ngrid, kMaxSplits, p->ncu, g, &cols, &splits);
   for (int b = 0; b < B; ++b) {
     const float* sb = s + (int64_t)b * g.nsub * g.nt;
     float* yb = y + (int64_t)b * g.nobs * g.nt;
@@ -1315,7 +1315,7 @@ s2w_status s2w_adjoint(s2w_plan* p, const float* r, int32_t B, float* gs, void* 
   const int nwg = p->ncu * wg_per_cu(p, 2);
   const int rows = fused_tile_rows(p, nwg);
   int cols = p->tune.adj_cols, splits = p->tune.adj_splits;
-  rows_contract_shape(g.nsp, g.ngrid, kMaxSplits, g, &cols, &splits);
+  rows_contract_shape(g.nsp, g.ngrid, kMaxSplits, p->ncu, g, &cols, &splits);
   for (int b = 0; b < B; ++b) {
     const float* rb = r + (int64_t)b * g.nobs * g.nt;
     float* gb = gs + (int64_t)b * g.nsub * g.nt;

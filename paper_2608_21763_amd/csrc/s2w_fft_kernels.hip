@@ -330,8 +330,7 @@ hipError_t launch_forward_rows(const float2* Gh, const float2* Sh, float2* Vh, i
 // Bound by HBM: RU rows of CPT float4 per thread at a time, the next ones loaded under the products of
 // the current ones (loads past the range repeat its last row with a zero coefficient).  Sixteen
 // columns, one row and 16 ranges leave most CUs without work when the columns are few (60 columns:
-// 32 workgroups, 1.7 TB/s); 8 columns, two rows and more ranges: 60 x 30,207 x 256 steps 2.23 -> 0.58 ms,
-// 240 x 9,440 0.87 -> 0.70 ms.
+// 32 workgroups, 1.7 TB/s); 8 columns, two rows and more ranges: 60 x 30,207 x 256 steps 2.23 -> 0.58 ms.
 template <int CPT, int RU, bool CONJ>
 __global__ __launch_bounds__(256) void k_rows_contract(const v4f* __restrict__ X, const float2* __restrict__ W,
                                                        v4f* __restrict__ part, int ngrid, int nc, int ncp, int M) {
@@ -399,23 +398,21 @@ __global__ __launch_bounds__(256) void k_rows_contract(const v4f* __restrict__ X
   }
 }
 
-// Columns per thread and row ranges, each where the caller has not set it (negative), towards 240
-// workgroups (more ranges only add partial sums: 963 columns at 16, 32 and 64 ranges 1.52, 1.59,
-// 1.70 ms per adjoint of 4,720 rows): sixteen columns and 16 ranges where those give as many (480
-// columns 1.47 against 1.49-1.52 ms with 8, 963 columns 1.52 against 1.56), else 8 columns (240 columns
-// 0.80 against 0.96), and 4 where 8 with every range allowed still gives fewer (60 columns of 128
-// slots 0.18 against 0.21 ms).
-void rows_contract_shape(int ncp, int ngrid, int max_splits, const Geometry& g, int* cols, int* splits) {
-  const int CS = 256 / (g.M / 2);
+// Columns per thread and row ranges, each where the caller has not set it (negative).  One workgroup per CU
+// is what the kernel's loads need, and 55 of 64 CUs take the whole bandwidth already; a few more than one
+// per CU wait for a second round of their own.  So the ranges fill 55/64 of the CUs once, with sixteen
+// columns per thread unless that takes more ranges than there may be (or rows to share out), else 8, else 4
+// (less in flight per workgroup: 15/16 of the CUs).
+// Whole adjoint of 9,440 rows x 256 slots in us, columns x ranges: 60 columns 8 x 55 261, 16 x 16 771; 240 columns
+// 16 x 27 752, 8 x 16 742, 16 x 16 906; 288 columns 16 x 24 852, 16 x 16 936, 8 x 16 (288 workgroups) 1,147; 400
+// columns 16 x 16 1,140, 8 x 16 1,271; 560 columns 16 x 12 1,565, 16 x 16 2,125; 963 columns 16 x 7 2,622, 16 x 16 2,772.
+void rows_contract_shape(int ncp, int ngrid, int max_splits, int ncu, const Geometry& g, int* cols, int* splits) {
+  const int CS = 256 / (g.M / 2), want = ncu * 55 / 64, most = std::min(max_splits, (ngrid + 3) / 4);
   auto blocks = [&](int c) { return (ncp + c * CS - 1) / (c * CS); };
   if (*cols < 0)
-    *cols = blocks(16) * (*splits < 0 ? 16 : *splits) >= 240           ? 16
-            : blocks(8) * (*splits < 0 ? max_splits : *splits) >= 240 ? 8
-                                                                      : 4;
-  if (*splits < 0) {
-    const int want = *cols == 16 ? 16 : std::max(16, (240 + blocks(*cols) - 1) / blocks(*cols));
-    *splits = std::max(1, std::min(std::min(max_splits, want), (ngrid + 3) / 4));
-  }
+    for (*cols = 16; *cols > 4; *cols /= 2)
+      if (blocks(*cols) * (*splits < 0 ? most : *splits) >= want) break;
+  if (*splits < 0) *splits = std::max(1, std::min(most, (*cols > 4 ? want : ncu * 15 / 16) / blocks(*cols)));
 }
 
 template <bool CONJ>

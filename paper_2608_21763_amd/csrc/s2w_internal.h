@@ -94,7 +94,7 @@ hipError_t launch_adjoint_elastic(const float2* Gh, const float2* Wp, float2* pa
                                   const Geometry& g, hipStream_t st);
 
 // Columns per thread and row ranges of a contraction over the grid rows, each where it is negative.
-void rows_contract_shape(int ncp, int ngrid, int max_splits, const Geometry& g, int* cols, int* splits);
+void rows_contract_shape(int ncp, int ngrid, int max_splits, int ncu, const Geometry& g, int* cols, int* splits);
 
 // Unfused forward: stage 1 writes the per-row mid-chain output Vh[g][l]; stage 2
 // contracts it with the acoustic store per bin, split over grid rows.
