@@ -20,6 +20,7 @@ namespace {
 constexpr uint64_t kAlign = 256;
 constexpr int kMaxWgPerCu = 4;
 constexpr int kMaxSplits = 64;
+constexpr size_t kLdsPerCu = 160 * 1024;
 
 inline uint64_t round_up(uint64_t v, uint64_t a) { return (v + a - 1) / a * a; }
 // Rupture stride of the workspace regions in a call of B ruptures (the regions are sized for
@@ -1201,26 +1202,31 @@ static uint64_t single_fused_scratch(const s2w_plan* p, int wg_per_cu, uint64_t*
 // Workgroups and tile rows of the fused forward, each by size unless the caller has set it.
 //   Two workgroups per CU hide each other's mid-chain where the operator rows are short next to it:
 //   30 subfaults x 37,760 rows x 4 observers x 256 slots 615 -> 481 us, 120 x 20,000 x 8 822 -> 788; but
-//   480 x 37,758 x 32 5,612 -> 5,814, and 60 x 3,000 x 4 has 12 rows per CU: 98 -> 102.  Not where their
-//   scratch is too much for s2w_forward_noalloc, which gives the same bits and serves those plans with one.
+//   480 x 37,758 x 32 5,612 -> 5,814, and 60 x 3,000 x 4 has 12 rows per CU: 98 -> 102.  Not where more than
+//   16 observers per thread leave registers for one of them only: 22 x 4,200 x 182 x 64 slots 108 -> 131, 150 x
+//   5,000 x 100 x 128 233 -> 271.  Not where their scratch is too much for s2w_forward_noalloc, which gives
+//   the same bits and serves those plans with one.
 //   Tiles of 4 rows take more time per row than tiles of 8 but waste less at the end of a workgroup's
-//   range: 963 x 4,720 x 64 1,580 -> 1,477 (20 rows for 24), 60 x 30,207 x 4 662 -> 692 (60 for 64).
+//   range: 963 x 4,720 x 64 1,580 -> 1,477 (20 rows for 24), 60 x 30,207 x 4 662 -> 692 (60 for 64).  At 512
+//   slots a tile of 8 rows takes 104 KB of the CU's LDS, so that two workgroups are resident with tiles of 4
+//   only: 30 x 20,000 x 14 738 -> 601, adjoint of 100 x 5,000 x 8 459 -> 410.
 struct FusedShape {
   int wg_per_cu, nwg, rows;
 };
-static int fused_tile_rows(const s2w_plan* p, int nwg) {
+static int fused_tile_rows(const s2w_plan* p, int wgs_per_cu) {
   if (p->tune.fused_rows > 0) return p->tune.fused_rows;
-  const int r = (p->geo.ngrid + nwg - 1) / nwg;
+  if (wgs_per_cu > 1 && wgs_per_cu * tile_lds(8, p->geo.M) > kLdsPerCu) return 4;
+  const int nwg = p->ncu * wgs_per_cu, r = (p->geo.ngrid + nwg - 1) / nwg;
   return (r + 3) / 4 * 4 * 100 <= (r + 7) / 8 * 8 * 93 ? 4 : 8;
 }
 static FusedShape fused_shape(const s2w_plan* p) {
   const Geometry& g = p->geo;
   uint64_t o = 0;
-  const bool two = g.nsub <= 160 && g.ngrid >= 16 * p->ncu &&
+  const bool two = g.nsub <= 160 && g.ngrid >= 16 * p->ncu && fused_forward_opt(g) <= 16 &&
                    single_fused_scratch(p, 2, &o, &o) <= (uint64_t)S2W_NOALLOC_SCRATCH_BYTES;
   FusedShape f{wg_per_cu(p, two ? 2 : 1), 0, 0};
   f.nwg = p->ncu * f.wg_per_cu;
-  f.rows = fused_tile_rows(p, f.nwg);
+  f.rows = fused_tile_rows(p, f.wg_per_cu);
   // no partial spectra without rows
   if (p->tune.fused_wg_per_cu < 0) f.nwg = std::min(f.nwg, (g.ngrid + f.rows - 1) / f.rows);
   return f;
@@ -1313,7 +1319,7 @@ s2w_status s2w_adjoint(s2w_plan* p, const float* r, int32_t B, float* gs, void* 
   // 512 slots take 0.85 (4 x 30,000 x 1 x 32, 201 -> 172 us) to 1.03 (16 x 1,000 x 64 x 256, 56 -> 58 us)
   // of the time with one
   const int nwg = p->ncu * wg_per_cu(p, 2);
-  const int rows = fused_tile_rows(p, nwg);
+  const int rows = fused_tile_rows(p, wg_per_cu(p, 2));
   int cols = p->tune.adj_cols, splits = p->tune.adj_splits;
   rows_contract_shape(g.nsp, g.ngrid, kMaxSplits, p->ncu, g, &cols, &splits);
   for (int b = 0; b < B; ++b) {

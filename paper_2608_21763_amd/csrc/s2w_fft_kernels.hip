@@ -177,7 +177,7 @@ static inline int next_pow2(int v) {
   return p;
 }
 
-static inline size_t tile_lds(int T, int M) {
+size_t tile_lds(int T, int M) {
   return 2 * (size_t)T * M * sizeof(float2) + 256 * (size_t)T * 16 + 2 * (size_t)M * sizeof(float2);
 }
 

@@ -82,6 +82,8 @@ hipError_t launch_sum_parts(const float2* part, int nparts, int64_t items_c, flo
 
 // Observers per thread the fused forward needs (it supports up to 32).
 int fused_forward_opt(const Geometry& g);
+// LDS bytes of a workgroup of the single-rupture row kernels at T rows per tile.
+size_t tile_lds(int T, int M);
 
 // Single-rupture adjoint, stage 1: per grid row, conj-transposed acoustic contraction,
 // mid-chain round trip with the transposed difference; Wp[g][slot] (complex).

@@ -1,6 +1,7 @@
-"""Grid-row contraction of the single layout where its shape rule turns: column counts with 16, 8 and 4 columns
+"""Single layout where its shape rules turn.  Grid-row contraction: column counts with 16, 8 and 4 columns
 per thread, with the fewest and the most row ranges, last column blocks that are not full, at every slot count
-it divides differently.  Bound: rel-L2 <= 1e-5 (the float32 bar) against the oracle, adjoint and, for many
+it divides differently.  Fused forward and the adjoint's row stage: one and two workgroups per CU on both sides
+of 16 observers per thread, and at 512 slots.  Bound: rel-L2 <= 1e-5 (the float32 bar) against the oracle, adjoint and, for many
 observers, the unfused forward.
 """
 import numpy as np
@@ -15,7 +16,8 @@ pytestmark = pytest.mark.gpu
 
 SHAPES = [(96, 300, 2, 130), (97, 300, 2, 130), (48, 300, 2, 130), (49, 300, 2, 130), (289, 260, 2, 130),
           (1024, 260, 1, 130), (200, 900, 2, 16), (768, 900, 1, 16), (1000, 300, 1, 40), (24, 260, 256, 260),
-          (24, 260, 140, 129), (1024, 230, 1, 300)]
+          (24, 260, 140, 129), (1024, 230, 1, 300),
+          (3, 4100, 128, 40), (3, 4100, 129, 40), (2, 4100, 2, 258), (2, 4100, 17, 257)]
 
 
 @pytest.mark.parametrize("shape", SHAPES, ids=["x".join(map(str, s)) for s in SHAPES])
