@@ -104,7 +104,7 @@ struct HalfGeo {
   int nsq, noq, ngq, nks;     // padded subfaults (x16), observers (16 * 2^k), grid rows (x16); K steps
   int bp;                     // max_batch padded to a multiple of 8
   int splits_max;
-  int rs;                     // setup rows per staging pass
+  int rs;                     // setup rows whose maxima are kept at a time
 };
 
 }  // namespace
@@ -291,7 +291,7 @@ Layout make_layout(const s2w_desc& d, const Geometry& g, const HalfGeo& h, const
     const uint64_t bp = (uint64_t)h.bp;
     const uint64_t ncb = bp / 8;
     L.staging = off;
-    off = round_up(off + (uint64_t)h.rs * g.M * std::max(h.nsq, h.noq) * c8, kAlign);
+    off = round_up(off + 2 * (uint64_t)h.rs * g.M * 4, kAlign);
     L.S = off;
     off = round_up(off + (uint64_t)g.M * h.nsq * bp * c8, kAlign);
     L.sig_up = off;
@@ -397,7 +397,7 @@ s2w_status s2w_plan_create(const s2w_desc* desc, int32_t device, s2w_plan** out)
     h.nks = h.nsq / 16;
     h.bp = (std::max(d.max_batch, 1) + 7) / 8 * 8;
     h.splits_max = 16;
-    h.rs = 16;
+    h.rs = std::min(d.ngrid, 4096);
   }
   if (batched32) {
     BatchGeo32& f = p->fb;
@@ -619,14 +619,10 @@ static s2w_status set_operators_half(s2w_plan* p, const float* G_chunk, const fl
     if (e != hipSuccess) return hip_fail(p, e, "set_operators: clear padding");
     p->pad_zeroed = true;
   }
-  uint32_t* mx = (uint32_t*)(p->ws + p->lay.staging);
-  const int64_t mx_words = 2 * (int64_t)h.rs * g.M * std::max(h.nsq, h.noq);
-  e = launch_quant_spectra(h.ht_g, true, G_chunk, nrows, g.nsub, h.nsq, Gq, row0, 0, 0, h.ngq / 16, sG, mx, mx_words, g,
-                           st);
-  if (e != hipSuccess) return hip_fail(p, e, "set_operators: elastic transform/quantize");
-  e = launch_quant_spectra(h.ht_f, false, F_chunk, nrows, g.nobs, h.noq, Fq, row0, h.ngq, (int64_t)h.noq * h.ngq, 0,
-                           sF, mx, mx_words, g, st);
-  if (e != hipSuccess) return hip_fail(p, e, "set_operators: acoustic transform/quantize");
+  const QuantStore G{h.ht_g, G_chunk, g.nsub, h.nsq, Gq, h.ngq / 16, 0, 0, sG};
+  const QuantStore F{h.ht_f, F_chunk, g.nobs, h.noq, Fq, 0, h.ngq, (int64_t)h.noq * h.ngq, sF};
+  e = launch_quant_spectra(G, F, nrows, row0, (uint32_t*)(p->ws + p->lay.staging), 2 * (int64_t)h.rs * g.M, g, st);
+  if (e != hipSuccess) return hip_fail(p, e, "set_operators: transform/quantize");
   return S2W_OK;
 }
 

@@ -57,13 +57,21 @@ hipError_t launch_irfft_units(const float2* part, int splits, int64_t p_s, int64
 bool sum_irfft_rows_fits(int M, int nparts);
 hipError_t launch_sum_irfft_rows(const float2* part, int nparts, int nrows, int nop, float* out, const Geometry& g,
                                  hipStream_t st);
-// Half-precision setup: spectra of in[row][col][nt] as scaled half words (ht: 1 = bf16, 2 = f16) with
-// one power-of-two scale per (grid row, slot), down[(row0 + row)*M + l].  Elastic: row-block-major
-// words (((l*nrb + g/16)*(ncp/16) + c/16)*16 + g%16)*16 + c%16; else word c*w_col + l*w_slot + g,
-// with g = row0 + row and columns ncols <= c < ncp zero.  mx: scratch of at least M words.
-hipError_t launch_quant_spectra(int ht, bool elastic, const float* in, int64_t nrows, int ncols, int ncp,
-                                uint32_t* out, int64_t row0, int64_t w_col, int64_t w_slot, int nrb, float* down,
-                                uint32_t* mx, int64_t mx_words, const Geometry& g, hipStream_t st);
+// Half-precision setup: spectra of time blocks in[row][cols][nt] as scaled half words (ht: 1 = bf16, 2 = f16)
+// with one power-of-two scale per (grid row, slot), its inverse at down[g*M + l], g = row0 + row.  Elastic
+// operator G: row-block-major words (((l*row_blocks + g/16)*(pad/16) + c/16)*16 + g%16)*16 + c%16; acoustic F:
+// word c*w_col + l*w_slot + g.  Columns cols <= c < pad are zero.  mx: scratch, 2 M words per row kept at a time.
+struct QuantStore {
+  int ht;
+  const float* in;
+  int cols, pad;
+  uint32_t* words;
+  int row_blocks;
+  int64_t w_col, w_slot;
+  float* down;
+};
+hipError_t launch_quant_spectra(const QuantStore& G, const QuantStore& F, int64_t nrows, int64_t row0, uint32_t* mx,
+                                int64_t mx_words, const Geometry& g, hipStream_t st);
 // Batched forms of M = 256: the forward real FFT of time rows in[b][j][n] into out[l][j][b] (l * out_slot
 // + j * bp + b), and the sum of split partials part[s][l][o][2 bp] with the inverse into out[b][o][n].
 hipError_t launch_rfft_batch256(const float* in, int B, int nrows, int nrows_pad, float2* out, int bp, int64_t out_slot,

@@ -36,11 +36,11 @@ struct RfftArgs {
   void* out;  // slot l of row (a, b) at out + a * oa + b * ob + l * ol
   int64_t oa, ob, ol;
   int nau, nbu;  // units along a and b
-  // OUT_MAX and the half words: the grid row is a (grid_a, columns along b) or b (columns along
-  // a).  A workgroup keeps one unit index (loop_b: that of a) and runs over one of `splits` ranges
-  // of the other
-  int grid_a, loop_b, splits, nfix;
-  uint32_t* mx;     // [grid row of this call][slot]: largest value (float bits), then its scale
+  // OUT_MAX and the half words: the grid row is a (elastic, columns along b) or b (columns along a).  A
+  // workgroup (of nwg) keeps one unit index of the grid rows and runs over one of `splits` ranges of the other
+  int elastic, splits, nfix, nwg;
+  uint32_t* mx;     // [grid row of this call][slot]: largest value (float bits)
+  float* down;      // inverse scales [grid row][slot]
   int64_t row0;
   int ncp16;        // elastic words: column blocks of 16 (row-block-major store); 0: strided words
 };
@@ -51,42 +51,40 @@ struct RfftArgs {
 // Bound by HBM at setup (4 nt bytes read, 4 or 8 M written per row) and by the latency of one unit on
 // few rows.  The register transform replaced a radix-4 one in LDS with a barrier per stage and 4- and
 // 8-byte strided stores: 512 grid rows of 963 + 64 columns x 256 steps into half words took 2.9 ms
-// (16 rows per launch), now 0.2 (maxima) + 0.25 (words) ms elastic and 0.08 ms acoustic; one unit of 16
-// short rows 12.6, now 3.8 us.
+// (16 rows per launch), now 0.51 ms in all; one unit of 16 short rows 12.6, now 3.8 us.
 template <int M, int OUT>
-__global__ __launch_bounds__(256, M <= 256 ? 3 : 2) void k_rfft_units(const RfftArgs p) {
+__device__ __forceinline__ void rfft_units(const RfftArgs& p, int wg, int nwg, float2* X, float2* twl) {
   using F = RowFft<M>;
   constexpr int LOGM = ilog2c(M), Q = F::GA * M / 16, H = F::N1 / 2;
   constexpr bool GW = OUT == OUT_G || OUT == OUT_G + 1, FW = OUT == OUT_F || OUT == OUT_F + 1;
   constexpr bool FIX = GW || FW || OUT == OUT_MAX;
   constexpr int HT = OUT == OUT_G || OUT == OUT_F ? 1 : 2;
-  __shared__ float2 X[F::ROWS * F::LD];
   const int tid = threadIdx.x;
   const int row = tid / F::TPR, c = tid % F::TPR, ga = row >> 4, br = row & 15;  // transform
   const int r = tid & 15, lq = tid >> 4;                                        // stores by run
   float2* Xr = X + row * F::LD;
-  __shared__ float2 twl[kTwLds<M>];
   fill_tw_lds<M>(twl);
   RowTw<M> tw;
   tw.init(c, twl);
   // units u = fixed * nloop + step; with FIX a workgroup's fixed index is its grid rows
-  const bool loop_b = !FIX || p.loop_b;
+  const bool loop_b = !FIX || p.elastic;
   const int nloop = loop_b ? p.nbu : p.nau;
   int64_t u, u1, du, f = 0;
+  int split = 0;
   if (FIX) {
     // workgroups go round the eight XCDs; neighbours in the fixed index (grid rows whose words
     // share cache lines) are given to one XCD
-    const int at = (int)((blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3));
+    const int at = (wg & 7) * (nwg >> 3) + (wg >> 3);
     if (at >= p.nfix * p.splits) return;
     f = at % p.nfix;
-    const int s = at / p.nfix;
-    u = f * nloop + (int64_t)nloop * s / p.splits;
-    u1 = f * nloop + (int64_t)nloop * (s + 1) / p.splits;
+    split = at / p.nfix;
+    u = f * nloop + (int64_t)nloop * split / p.splits;
+    u1 = f * nloop + (int64_t)nloop * (split + 1) / p.splits;
     du = 1;
   } else {
-    u = blockIdx.x;
+    u = wg;
     u1 = (int64_t)p.nau * p.nbu;
-    du = gridDim.x;
+    du = nwg;
   }
   if (kTwLds<M> > 1) __syncthreads();  // the twiddle table
   const bool even = !(p.nt & 1);
@@ -117,23 +115,23 @@ __global__ __launch_bounds__(256, M <= 256 ? 3 : 2) void k_rfft_units(const Rfft
         pv[j][n1] = xv;
       }
   };
-  // half words: scale multipliers of this thread's stores.  Elastic words leave four columns (16
-  // bytes) at a time, thread -> column quad tid % 4 of slot and grid row (tid / 4 + 64 k); the
-  // acoustic ones by single words (their alignment is the caller's first row's)
+  // half words: scale multipliers of this thread's stores, the same in all its units; the first range of
+  // the grid rows leaves the inverses.  Elastic words go four columns (16 bytes) at a time, thread -> column
+  // quad tid % 4 of slot and grid row (tid / 4 + 64 k); the acoustic ones by single words (their
+  // alignment is the caller's first row's)
   constexpr int NUP = GW ? Q / 4 : (FW ? Q : 1);
   float up[NUP];
-  auto scales = [&](int a0, int b0) {
-#pragma unroll
-    for (int k = 0; k < NUP; ++k) {
-      const int q = GW ? (tid >> 2) + 64 * k : lq + 16 * k;
-      const int g = GW ? min(a0 + (q >> LOGM), p.na - 1) : min(b0 + r, p.nb - 1);
-      up[k] = __uint_as_float(p.mx[(int64_t)g * M + (q & (M - 1))]);
-    }
-  };
-  if (FW && u < u1) {  // its grid rows are kept
+  if ((GW || FW) && u < u1) {
     int a0, b0;
     unit(u, a0, b0);
-    scales(a0, b0);
+#pragma unroll
+    for (int k = 0; k < NUP; ++k) {
+      const int q = GW ? (tid >> 2) + 64 * k : lq + 16 * k, l = q & (M - 1);
+      const int g = GW ? a0 + (q >> LOGM) : b0 + r, ng = GW ? p.na : p.nb;
+      float dn;
+      pow2_scale(__uint_as_float(p.mx[(int64_t)min(g, ng - 1) * M + l]), up[k], dn);
+      if (split == 0 && g < ng && (GW ? (tid & 3) == 0 : q < M)) p.down[(p.row0 + g) * M + l] = dn;
+    }
   }
   float mx[OUT == OUT_MAX ? F::E : 1];
   if (OUT == OUT_MAX) {
@@ -150,7 +148,6 @@ __global__ __launch_bounds__(256, M <= 256 ? 3 : 2) void k_rfft_units(const Rfft
 #pragma unroll
       for (int n1 = 0; n1 < H; ++n1) v[j][n1] = make_float2(pv[j][n1].x * p.scale, pv[j][n1].y * p.scale);
     if (u + du < u1) fetch(u + du);
-    if (GW) scales(a0, b0);
     row_forward<M>(Xr, c, tw, v);
     if (OUT == OUT_MAX) {
 #pragma unroll
@@ -201,31 +198,64 @@ __global__ __launch_bounds__(256, M <= 256 ? 3 : 2) void k_rfft_units(const Rfft
     __syncthreads();  // the next unit refills X
   }
   if (OUT == OUT_MAX) {
-    const int64_t g = p.grid_a ? f * F::GA + ga : f * 16 + br;
+    // the rows of one grid row together through LDS, then one atomic per grid row and slot
+    float* W = reinterpret_cast<float*>(X);
+    __syncthreads();
 #pragma unroll
-    for (int e = 0; e < F::E; ++e) {
-      float m = mx[e];
-      if (p.grid_a) {  // the wavefront's rows belong to one grid row
-#pragma unroll
-        for (int s = F::TPR; s < 64; s <<= 1) m = fmaxf(m, __shfl_xor(m, s, 64));
-        if ((tid & 63) < F::TPR && g < p.na) atomicMax(p.mx + g * M + c + F::TPR * e, __float_as_uint(m));
-      } else if (g < p.nb) {
-        atomicMax(p.mx + g * M + c + F::TPR * e, __float_as_uint(m));
-      }
+    for (int e = 0; e < F::E; ++e) W[row * M + c + F::TPR * e] = mx[e];
+    __syncthreads();
+    const int ng = p.elastic ? F::GA : 16, nr = p.elastic ? 16 : F::GA;  // grid rows of a unit, rows of each
+    for (int i = tid; i < ng * M; i += 256) {
+      const int gr = i >> LOGM, l = i & (M - 1);
+      float m = 0.f;
+      for (int k = 0; k < nr; ++k) m = fmaxf(m, W[(p.elastic ? gr * 16 + k : k * 16 + gr) * M + l]);
+      const int64_t g = f * ng + gr;
+      if (g < (p.elastic ? p.na : p.nb)) atomicMax(p.mx + g * M + l, __float_as_uint(m));
     }
   }
 }
 
-// Power-of-two scales of the grid rows' words: mx[i] from the largest value (float bits) to the
-// multiplier, its inverse to down[i].
-__global__ __launch_bounds__(256) void k_row_scales(uint32_t* __restrict__ mx, int64_t n, float* __restrict__ down) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n) return;
-  float up, dn;
-  pow2_scale(__uint_as_float(mx[i]), up, dn);
-  mx[i] = __float_as_uint(up);
-  down[i] = dn;
+#define S2W_RFFT_LDS(M_)                                        \
+  __shared__ float2 X[RowFft<M_>::ROWS * RowFft<M_>::LD];       \
+  __shared__ float2 twl[kTwLds<M_>]
+
+template <int M, int OUT>
+__global__ __launch_bounds__(256, M <= 256 ? 3 : 2) void k_rfft_units(const RfftArgs p) {
+  S2W_RFFT_LDS(M);
+  rfft_units<M, OUT>(p, blockIdx.x, gridDim.x, X, twl);
 }
+
+// Half-precision setup, both operators in one launch, the elastic one by the first workgroups: the maxima of the grid
+// rows, and their words.
+template <int M>
+__global__ __launch_bounds__(256, M <= 256 ? 3 : 2) void k_rfft_max(const RfftArgs g, const RfftArgs f) {
+  S2W_RFFT_LDS(M);
+  const bool e = (int)blockIdx.x < g.nwg;
+  RfftArgs p{};
+  p.in = e ? g.in : f.in;
+  p.in_a = e ? g.in_a : f.in_a;
+  p.in_b = e ? g.in_b : f.in_b;
+  p.na = e ? g.na : f.na;
+  p.nb = e ? g.nb : f.nb;
+  p.nt = g.nt;
+  p.scale = g.scale;
+  p.nau = e ? g.nau : f.nau;
+  p.nbu = e ? g.nbu : f.nbu;
+  p.elastic = e;
+  p.splits = e ? g.splits : f.splits;
+  p.nfix = e ? g.nfix : f.nfix;
+  p.mx = e ? g.mx : f.mx;
+  rfft_units<M, OUT_MAX>(p, e ? blockIdx.x : blockIdx.x - g.nwg, e ? g.nwg : f.nwg, X, twl);
+}
+template <int M, int HG, int HF>
+__global__ __launch_bounds__(256, M <= 256 ? 3 : 2) void k_rfft_words(const RfftArgs g, const RfftArgs f) {
+  S2W_RFFT_LDS(M);
+  if ((int)blockIdx.x < g.nwg)
+    rfft_units<M, OUT_G + HG - 1>(g, blockIdx.x, g.nwg, X, twl);
+  else
+    rfft_units<M, OUT_F + HF - 1>(f, blockIdx.x - g.nwg, f.nwg, X, twl);
+}
+#undef S2W_RFFT_LDS
 
 // Inverse real FFT (Alg. 2 steps 4-5: keep n < nt) of summed partial spectra,
 //   out[b * ob + a * oa + n] = scale * IFFT(tau[l][b] * sum_s part[s * p_s + a * pa + b * pb + l * pl])[n].
@@ -617,63 +647,75 @@ hipError_t launch_rfft_units(const float* in, int64_t in_a, int64_t in_b, int na
   return hipGetLastError();
 }
 
-hipError_t launch_quant_spectra(int ht, bool elastic, const float* in, int64_t nrows, int ncols, int ncp,
-                                uint32_t* out, int64_t row0, int64_t w_col, int64_t w_slot, int nrb, float* down,
-                                uint32_t* mx, int64_t mx_words, const Geometry& g, hipStream_t st) {
-  if (g.nt < 1 || g.nt > g.M || ncp < ncols || (elastic && ncp % 16) || mx_words < g.M) return hipErrorInvalidValue;
-  // a pass over the largest |Re|, |Im| of every (grid row, slot), then one that writes the scaled
-  // words: the transform is done twice instead of keeping 8-byte spectra between the passes
+// One operator's side of the setup: n grid rows from in[row][c.cols][nt], in `wgs` workgroups at least where there
+// are that many units.
+static RfftArgs quant_args(const QuantStore& c, bool elastic, const float* in, int n, int64_t row0, uint32_t* mx,
+                           const Geometry& g) {
   const int ga = rows_ga(g.M);
+  RfftArgs a{};
+  a.in = in;
+  a.elastic = elastic;
+  a.in_a = elastic ? (int64_t)c.cols * g.nt : g.nt;
+  a.in_b = elastic ? g.nt : (int64_t)c.cols * g.nt;
+  a.na = elastic ? n : c.cols;
+  a.na_out = elastic ? n : c.pad;
+  a.nb = elastic ? c.cols : n;
+  a.nb_out = elastic ? c.pad : n;
+  a.nt = g.nt;
+  a.scale = 1.f;
+  a.out = c.words;
+  a.oa = c.w_col;
+  a.ol = elastic ? (int64_t)c.row_blocks * (c.pad / 16) * 256 : c.w_slot;
+  a.ncp16 = c.pad / 16;
+  a.nau = (a.na_out + ga - 1) / ga;
+  a.nbu = (a.nb_out + 15) / 16;
+  a.mx = mx;
+  a.down = c.down;
+  a.row0 = row0;
+  return a;
+}
+static void quant_grid(RfftArgs& a, int wgs) {
+  const int nloop = a.elastic ? a.nbu : a.nau;
+  a.nfix = a.elastic ? a.nau : a.nbu;
+  a.splits = std::max(1, std::min(nloop, (wgs + a.nfix - 1) / a.nfix));
+  // a multiple of eight, so that every XCD gets a whole share (the rest returns at once)
+  a.nwg = (int)(((int64_t)a.nfix * a.splits + 7) / 8 * 8);
+}
+
+hipError_t launch_quant_spectra(const QuantStore& G, const QuantStore& F, int64_t nrows, int64_t row0, uint32_t* mx,
+                                int64_t mx_words, const Geometry& g, hipStream_t st) {
+  if (g.nt < 1 || g.nt > g.M || G.pad < G.cols || F.pad < F.cols || G.pad % 16 || mx_words < 2 * g.M)
+    return hipErrorInvalidValue;
+  // a pass over the largest |Re|, |Im| of every (grid row, slot), then one that writes the scaled
+  // words: the transform is done twice instead of keeping 8-byte spectra between the passes.  Three launches,
+  // both operators in one: a few rows are a chain of launches and of one unit's latency
+  // (963 + 64 columns x 256 steps, 1, 16 and 512 rows:
+  // 19, 43 and 514 us, with eight launches 39, 62 and 544; 16 + 4 x 16, 1 row: 12, with eight 26).
   for (int64_t r0 = 0; r0 < nrows;) {
-    const int64_t n = std::min<int64_t>(nrows - r0, std::min<int64_t>(mx_words / g.M, 1 << 20));
-    hipError_t e = launch_zero_strided(mx, n * g.M, 1, 1, st);
+    const int n = (int)std::min<int64_t>(nrows - r0, mx_words / (2 * g.M));
+    hipError_t e = launch_zero_strided(mx, 2 * (int64_t)n * g.M, 1, 1, st);
     if (e != hipSuccess) return e;
-    RfftArgs a{};
-    a.in = in + r0 * ncols * g.nt;
-    a.grid_a = elastic ? 1 : 0;
-    a.in_a = elastic ? (int64_t)ncols * g.nt : g.nt;
-    a.in_b = elastic ? g.nt : (int64_t)ncols * g.nt;
-    a.na = elastic ? (int)n : ncols;
-    a.na_out = elastic ? (int)n : ncp;
-    a.nb = elastic ? ncols : (int)n;
-    a.nb_out = elastic ? ncp : (int)n;
-    a.nt = g.nt;
-    a.scale = 1.f;
-    a.out = out;
-    a.oa = w_col;
-    a.ol = elastic ? (int64_t)nrb * (ncp / 16) * 256 : w_slot;
-    a.ncp16 = ncp / 16;
-    a.nau = (a.na_out + ga - 1) / ga;
-    a.nbu = (a.nb_out + 15) / 16;
-    a.mx = mx;
-    a.row0 = row0 + r0;
-    // `wgs` workgroups at least where there are that many units
-    auto grid = [&](bool loop_b, int wgs) {
-      const int nloop = loop_b ? a.nbu : a.nau;
-      a.nfix = loop_b ? a.nau : a.nbu;
-      a.loop_b = loop_b;
-      a.splits = std::max(1, std::min(nloop, (wgs + a.nfix - 1) / a.nfix));
-      // a multiple of eight, so that every XCD gets a whole share (the rest returns at once)
-      return dim3((unsigned)(((int64_t)a.nfix * a.splits + 7) / 8 * 8));
-    };
-    // maxima: the grid rows are kept, their columns run.  Elastic words: the 16 columns are kept
-    // and the grid rows run, so that the 64-byte runs of consecutive rows, neighbours in the
-    // row-block-major store, follow each other in one L2
-    const dim3 gm = grid(elastic, 4096), gs((unsigned)((n * g.M + 255) / 256));
-#define S2W_CALL(M_) hipLaunchKernelGGL((k_rfft_units<M_, OUT_MAX>), gm, dim3(256), 0, st, a)
+    RfftArgs a = quant_args(G, true, G.in + r0 * G.cols * g.nt, n, row0 + r0, mx, g);
+    RfftArgs b = quant_args(F, false, F.in + r0 * F.cols * g.nt, n, row0 + r0, mx + (int64_t)n * g.M, g);
+    quant_grid(a, 4096);
+    quant_grid(b, 4096);
+#define S2W_CALL(M_) hipLaunchKernelGGL((k_rfft_max<M_>), dim3((unsigned)(a.nwg + b.nwg)), dim3(256), 0, st, a, b)
     S2W_BY_M(g.M, S2W_CALL)
 #undef S2W_CALL
-    hipLaunchKernelGGL(k_row_scales, gs, dim3(256), 0, st, mx, n * g.M, down + a.row0 * g.M);
-    const dim3 gw = grid(elastic, elastic ? 1536 : 4096);
-#define S2W_QUANT(M_, OUT_) hipLaunchKernelGGL((k_rfft_units<M_, OUT_>), gw, dim3(256), 0, st, a)
+    // Both word passes keep the grid rows too, consecutive ones on one XCD: their 64-byte runs (elastic,
+    // row-block-major) or single words (acoustic) are neighbours in the store and meet in one L2
+    quant_grid(a, 1536);
+    const dim3 grid((unsigned)(a.nwg + b.nwg));
+#define S2W_WORDS(M_, G_, F_) hipLaunchKernelGGL((k_rfft_words<M_, G_, F_>), grid, dim3(256), 0, st, a, b)
 #define S2W_CALL(M_)                                                  \
-  if (elastic) {                                                      \
-    if (ht == 1) S2W_QUANT(M_, OUT_G); else S2W_QUANT(M_, OUT_G + 1); \
+  if (G.ht == 1) {                                                    \
+    if (F.ht == 1) S2W_WORDS(M_, 1, 1); else S2W_WORDS(M_, 1, 2);     \
   } else {                                                            \
-    if (ht == 1) S2W_QUANT(M_, OUT_F); else S2W_QUANT(M_, OUT_F + 1); \
+    if (F.ht == 1) S2W_WORDS(M_, 2, 1); else S2W_WORDS(M_, 2, 2);     \
   }
     S2W_BY_M(g.M, S2W_CALL)
 #undef S2W_CALL
+#undef S2W_WORDS
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     r0 += n;
