@@ -10,6 +10,7 @@
 
 #include "s2w_half.h"
 #include "s2w_internal.h"
+#include "s2w_wave.h"
 
 namespace s2w {
 
@@ -132,6 +133,7 @@ __global__ __launch_bounds__(512) void k_gemm_gs(const uint4* __restrict__ Gq, c
       const int r = i / (4 * NF), c = i - r * (4 * NF);
       __builtin_nontemporal_store(from[i], reinterpret_cast<f32x4*>(U + (gf + r) * u_g + l * u_l) + c);
     }
+    wave_sync();  // other lanes of this wavefront write the next unit's products over what the burst reads
   };
   Group f0, f1;
   load(f0);

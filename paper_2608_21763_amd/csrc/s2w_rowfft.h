@@ -16,6 +16,7 @@
 #pragma once
 
 #include "s2w_device.h"
+#include "s2w_wave.h"
 
 namespace s2w {
 
@@ -33,13 +34,6 @@ struct RowFft {
   static constexpr int LD = (N1 * (N2 + 1)) | 1;        // row stride in LDS (odd: column reads spread)
   static_assert(CA * N1 == E && CB * N2 == E && TPR * CB == N1, "row split");
 };
-
-// Orders the LDS accesses of one wavefront's lanes (the hardware runs them in issue order).
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 // a * w (DIR < 0) or a * conj(w), with the rounding fixed: the product with Im w is rounded, the one
 // with Re w is fused.
