@@ -65,10 +65,10 @@ struct Layout {
   // workspace (float32 single-rupture path)
   uint64_t sh, part, yh, rh, wp, part2, gsh;
   // workspace (batched half-precision path)
-  uint64_t staging, S, sig_up, sig_down, bop, U, tau_up, tau_down, part_f, yhb;
+  uint64_t staging, S, sig_up, sig_down, bop, U, tau_up, tau_down, part_f;
   // operator store and workspace (batched float32 path)
   uint64_t gs, fs;
-  uint64_t s32, u32, part32, yh32;
+  uint64_t s32, u32, part32;
   // operator store and workspace (direct time-domain path)
   uint64_t gt, ft;
   uint64_t dpart, dv, dout;
@@ -248,8 +248,6 @@ Layout make_layout(const s2w_desc& d, const Geometry& g, const HalfGeo& h, const
     L.part32 = off;
     const uint64_t prow = std::max((uint64_t)f.splits_f_max * f.nok, (uint64_t)f.splits_a_max * f.nsk);
     off = round_up(off + prow * g.M * 2 * bp * 4, kAlign);
-    L.yh32 = off;
-    off = round_up(off + bp * std::max(g.nobs, g.nsub) * g.M * c8, kAlign);
     L.ws_total = off;
     return L;
   }
@@ -308,8 +306,6 @@ Layout make_layout(const s2w_desc& d, const Geometry& g, const HalfGeo& h, const
     off = round_up(off + (uint64_t)g.M * bp * 4, kAlign);
     L.part_f = off;  // acoustic partials; the adjoint's residual spectra and elastic partials
     off = round_up(off + (uint64_t)std::max(h.splits_max * h.noq, h.nsq) * g.M * 2 * bp * 4, kAlign);
-    L.yhb = off;
-    off = round_up(off + bp * g.nobs * g.M * c8, kAlign);
   }
   L.ws_total = off;
   (void)d;
@@ -1376,6 +1372,8 @@ s2w_status bhip(s2w_bltt* p, hipError_t e, const char* what) {
   return bfail(p, S2W_EHIP, "%s: %s", what, hipGetErrorString(e));
 }
 
+constexpr int kFewInputs = 4;  // apply: matrix-vector products up to this many
+
 // grid-row splits of a product with `rows` output rows: enough workgroups to fill the chip
 int bltt_splits(int M, int rows) {
   const int64_t tiles = (int64_t)M * ((rows + 63) / 64);
@@ -1428,8 +1426,8 @@ s2w_status s2w_bltt_create(const s2w_bltt_desc* desc, int32_t device, s2w_bltt**
   p->o_part = off;
   const uint64_t prow = std::max((uint64_t)p->splits_f * p->nrow_k, (uint64_t)p->splits_a * p->ncol_k);
   off = round_up(off + prow * M * 2 * bp * 4, kAlign);
-  p->o_yh = off;
-  off = round_up(off + bp * std::max(d.nrow, d.ncol) * M * c8, kAlign);
+  p->o_yh = off;  // apply of up to four inputs: their output spectra
+  off = round_up(off + (uint64_t)std::min(d.max_batch, kFewInputs) * d.nrow * M * c8, kAlign);
   p->ws_total = off;
   p->row_set.assign((size_t)d.nrow, 0);
   p->rows_missing = d.nrow;
@@ -1523,7 +1521,7 @@ s2w_status s2w_bltt_apply(s2w_bltt* p, const float* x, int32_t B, float* y, void
   float2* S = (float2*)(p->ws + p->o_s);
   float* part = (float*)(p->ws + p->o_part);
   float2* yh = (float2*)(p->ws + p->o_yh);
-  if (B <= 4) {
+  if (B <= kFewInputs) {
     // few inputs: per-bin matrix-vector products streaming the store once (HBM-bound);
     // inputs transformed as S[b][l][c]
     hipError_t e = launch_rfft_units(x, (int64_t)ncol * g.nt, g.nt, B, B, ncol, p->ncol_k, S,
