@@ -844,8 +844,8 @@ static s2w_status forward_half(s2w_plan* p, const float* s, int32_t B, float* y,
   // float16 acoustic operands: the column scales come from maxima the mid-chain keeps as it writes
   int groups = 0;
   if (flat)
-    e = g.M == 256 ? launch_mid_flat256(U, sF, B, bp, false, g, st, part, part_floats(p), &groups)
-                   : launch_mid_flat(U, sF, B, bp, false, g, st, part, part_floats(p), &groups);
+    e = g.M == 256 ? launch_mid_flat256(U, sF, B, bp, g, st, part, part_floats(p), &groups)
+                   : launch_mid_flat(U, sF, B, bp, g, st, part, part_floats(p), &groups);
   else
     e = mid_chain(p, U, sF, B, bp, false, fstaged, st, fscale ? part : nullptr, part_floats(p), &groups, disp);
   if (e != hipSuccess) return hip_fail(p, e, "forward: mid-chain");

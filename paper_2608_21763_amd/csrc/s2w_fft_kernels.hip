@@ -800,12 +800,11 @@ hipError_t launch_mid_batch256(float2* U, const float* sF, int B, int bp, bool a
   return hipGetLastError();
 }
 
-hipError_t launch_mid_flat256(float2* U, const float* sF, int B, int bp, bool adjoint, const Geometry& g,
-                              hipStream_t st, float* cmax, int64_t cmax_floats, int* cmax_groups) {
+hipError_t launch_mid_flat256(float2* U, const float* sF, int B, int bp, const Geometry& g, hipStream_t st,
+                              float* cmax, int64_t cmax_floats, int* cmax_groups) {
   if (g.M != 256 || (bp != 8 && bp != 16) || B < 1 || B > bp || g.nt > 256 || !cmax ||
       (int64_t)g.ngrid * bp > (1 << 24))
     return hipErrorInvalidValue;
-  const int mode = g.diff ? (adjoint ? MID_BACKWARD_T : MID_BACKWARD) : MID_NONE;
   const float mscale = (float)(1.0 / ((double)g.L * (g.diff ? (double)g.dt : 1.0)));
   const int64_t units = ((int64_t)g.ngrid * bp + 15) / 16;
   const int64_t nblk = std::min<int64_t>(std::min<int64_t>(units, 256 * 4), cmax_floats / ((int64_t)g.M * bp));
@@ -814,8 +813,7 @@ hipError_t launch_mid_flat256(float2* U, const float* sF, int B, int bp, bool ad
 #define S2W_FLAT(M_)                                                                                               \
   hipLaunchKernelGGL((k_mid_batch256<0, 16, false, M_, true>), dim3((unsigned)nblk), dim3(256), 0, st, U, sF, g.ngrid, \
                      B, bp, g.nt, mscale, cmax, DispOut{})
-  if (mode == MID_BACKWARD) S2W_FLAT(MID_BACKWARD);
-  else if (mode == MID_BACKWARD_T) S2W_FLAT(MID_BACKWARD_T);
+  if (g.diff) S2W_FLAT(MID_BACKWARD);
   else S2W_FLAT(MID_NONE);
 #undef S2W_FLAT
   return hipGetLastError();

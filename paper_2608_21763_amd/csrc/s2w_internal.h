@@ -167,11 +167,11 @@ hipError_t launch_mid_batch256(float2* U, const float* sF, int B, int bp, bool a
 hipError_t launch_mid_units(float2* U, const float* sF, int B, int bp, bool adjoint, bool pack_bf16,
                             const Geometry& g, hipStream_t st, float* cmax, int64_t cmax_floats, int* cmax_groups,
                             const DispOut* disp);
-// The same on U[l][g][b] with bp 8 or 16, maxima always (no packing, no displacement).
-hipError_t launch_mid_flat256(float2* U, const float* sF, int B, int bp, bool adjoint, const Geometry& g,
-                              hipStream_t st, float* cmax, int64_t cmax_floats, int* cmax_groups);
-hipError_t launch_mid_flat(float2* U, const float* sF, int B, int bp, bool adjoint, const Geometry& g, hipStream_t st,
-                           float* cmax, int64_t cmax_floats, int* cmax_groups);
+// The forward one on U[l][g][b] with bp 8 or 16, maxima always (no packing, no displacement).
+hipError_t launch_mid_flat256(float2* U, const float* sF, int B, int bp, const Geometry& g, hipStream_t st,
+                              float* cmax, int64_t cmax_floats, int* cmax_groups);
+hipError_t launch_mid_flat(float2* U, const float* sF, int B, int bp, const Geometry& g, hipStream_t st, float* cmax,
+                           int64_t cmax_floats, int* cmax_groups);
 // Power-of-two column scales from partial maxima part[s][l][b], s < splits (columns b >= B get 1).
 hipError_t launch_col_scale_final(const float* part, int splits, int M, int B, int bp, float* tau_up, float* tau_down,
                                   hipStream_t st);

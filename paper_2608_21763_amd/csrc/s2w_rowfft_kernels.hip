@@ -829,8 +829,8 @@ hipError_t launch_mid_units(float2* U, const float* sF, int B, int bp, bool adjo
   return hipGetLastError();
 }
 
-hipError_t launch_mid_flat(float2* U, const float* sF, int B, int bp, bool adjoint, const Geometry& g, hipStream_t st,
-                           float* cmax, int64_t cmax_floats, int* cmax_groups) {
+hipError_t launch_mid_flat(float2* U, const float* sF, int B, int bp, const Geometry& g, hipStream_t st, float* cmax,
+                           int64_t cmax_floats, int* cmax_groups) {
   if ((bp != 8 && bp != 16) || B < 1 || B > bp || g.nt > g.M || !cmax || (int64_t)g.ngrid * bp > (1 << 24))
     return hipErrorInvalidValue;
   const int rows = 16 * rows_ga(g.M);
@@ -841,7 +841,7 @@ hipError_t launch_mid_flat(float2* U, const float* sF, int B, int bp, bool adjoi
   a.B = B;
   a.bp = bp;
   a.nt = g.nt;
-  a.mode = g.diff ? (adjoint ? MID_BACKWARD_T : MID_BACKWARD) : MID_NONE;
+  a.mode = g.diff ? MID_BACKWARD : MID_NONE;
   a.mscale = (float)(1.0 / ((double)g.L * (g.diff ? (double)g.dt : 1.0)));
   a.cmax = cmax;
   a.nbb = 1;
