@@ -356,7 +356,7 @@ def main():
         # lag products of the elastic sum: Ngrid x Nsub pairs, Nt (Nt + 1) / 2 products each, 2 flops
         flops_g = 2.0 * cfg.ngrid * cfg.nsub * cfg.nt * (cfg.nt + 1) / 2
         flops_all = flops_g * (cfg.nsub + cfg.nobs) / cfg.nsub
-        dres = {"ruptures_per_s": 1000.0 / ms_step, "ms_per_step": ms_step, "B": 1, "kernel": "k_direct<2>",
+        dres = {"ruptures_per_s": 1000.0 / ms_step, "ms_per_step": ms_step, "B": 1, "kernel": "k_direct<2, 1>",
                 "kernel_ms": kmean, "algorithmic_flops_elastic": flops_g, "algorithmic_flops": flops_all,
                 "achieved_TFLOPs": flops_g / (kmean * 1e9),
                 "mfma_frac": flops_g / (kmean * 1e9) / MFMA_PEAK["f32"],
