@@ -267,9 +267,7 @@ hipError_t launch_direct(int rw, const float* A, int64_t a_c, int64_t a_r, int R
 // correlation, D_t^T (the adjoint); at the end it sums the output partials.  In the forward map
 // S is the seafloor displacement m of eq. (1), which `disp` may capture at selected steps.
 // A thread sums four consecutive steps (16-byte loads; p_s and p_r are multiples of 4, partial rows
-// whole fours).  Up to 16 partials it takes them all; the many partials of few rows are dealt to PL
-// threads and their sums added through LDS, in order.  One step per thread and all partials in one
-// chain took 42 us for 13 partials of 9,440 x 200 and 122 us for 512 of 16 x 200; now 20 and 6.
+// whole fours).  The partials are dealt to PL threads and their sums added through LDS, in order.
 template <int PL>
 __global__ __launch_bounds__(256) void k_direct_reduce(const float* __restrict__ part, int parts, int64_t p_s,
                                                        int64_t p_r, int R, int nt, int rev, int diff, float scale,
@@ -324,12 +322,21 @@ hipError_t launch_direct_reduce(const float* part, int parts, int64_t p_s, int64
     return hipErrorInvalidValue;
   const int64_t items = (int64_t)R * ((nt + 3) / 4);
   const DispOut d = disp ? *disp : DispOut{};
-  if (parts <= 16)
-    hipLaunchKernelGGL((k_direct_reduce<1>), dim3((unsigned)((items + 255) / 256)), dim3(256), 0, st, part, parts, p_s,
-                       p_r, R, nt, rev ? 1 : 0, diff ? 1 : 0, scale, out, o_r, d);
-  else
-    hipLaunchKernelGGL((k_direct_reduce<32>), dim3((unsigned)((items + 7) / 8)), dim3(256), 0, st, part, parts, p_s, p_r,
-                       R, nt, rev ? 1 : 0, diff ? 1 : 0, scale, out, o_r, d);
+  // Threads per sum: as many as 860 workgroups allow, a chain of all partials in one thread where the rows fill the
+  // chip by themselves.  us with 1 / 4 / 8 / 16 / 32 (one step per thread and all partials in one chain): 16 x 200, 512
+  // partials 78 / 23 / 13 / 8 / 5 (122); 300 x 100, 170 partials 29 / 10 / 7 / 7 / 10 (43); 200 x 512, 128 partials 31 / 12 /
+  // 10 / 11 / 26 (48); 964 x 374, 32 partials 9 / 9 / 10 / 12 / 40 (12); 9,440 x 200, 13 partials 19 / 20 / 21 / 33 / 194 (35).
+  int pl = 32;
+  while (pl > 1 && (pl > parts || items * pl > 860 * 256)) pl = pl == 4 ? 1 : pl / 2;
+#define S2W_REDUCE(PL_)                                                                                               \
+  hipLaunchKernelGGL((k_direct_reduce<PL_>), dim3((unsigned)((items + 256 / PL_ - 1) / (256 / PL_))), dim3(256), 0, st, \
+                     part, parts, p_s, p_r, R, nt, rev ? 1 : 0, diff ? 1 : 0, scale, out, o_r, d)
+  if (pl == 32) S2W_REDUCE(32);
+  else if (pl == 16) S2W_REDUCE(16);
+  else if (pl == 8) S2W_REDUCE(8);
+  else if (pl == 4) S2W_REDUCE(4);
+  else S2W_REDUCE(1);
+#undef S2W_REDUCE
   return hipGetLastError();
 }
 
