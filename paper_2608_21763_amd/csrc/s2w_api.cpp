@@ -871,7 +871,9 @@ static s2w_status forward_half(s2w_plan* p, const float* s, int32_t B, float* y,
 }
 
 // Tile of a batched float32 product: the caller's choice, else by its rows and the batch.
-static int b32_cfg(int tuned, int nrows, int B) { return tuned >= 0 ? tuned : cgemm32_pick(nrows, B); }
+static int b32_cfg(const s2w_plan* p, int tuned, int nrows, int B, int splits) {
+  return tuned >= 0 ? tuned : cgemm32_pick(nrows, B, (int64_t)p->geo.M * splits, p->ncu);
+}
 
 // Tile that sets the number of grid-row ranges of a reduction where the caller has chosen none: by the
 // batch alone, so that the grouping of the sums does not move with the rules of cgemm32_pick.
@@ -903,7 +905,7 @@ static s2w_status forward_b32(s2w_plan* p, const float* s, int32_t B, float* y, 
   hipError_t e = rfft_batch(s, B, g.nsub, f.nsk, S, bp, g, st);
   if (e != hipSuccess) return hip_fail(p, e, "forward: source transform");
   // U[g][l][b] = sum_j Gs[g][l][j] S[l][j][b]
-  const int cg = b32_cfg(p->tune.gemm32_cfg, g.ngrid, B);
+  const int cg = b32_cfg(p, p->tune.gemm32_cfg, g.ngrid, B, 1);
   e = mark(p->ev_begin, st);
   if (e == hipSuccess)
     e = launch_cgemm32(cg, false, Gs, (int64_t)g.M * f.nsk, 1, f.nsk, g.ngrid, g.ngrid, f.nsk, f.nsk, S, bp,
@@ -914,10 +916,11 @@ static s2w_status forward_b32(s2w_plan* p, const float* s, int32_t B, float* y, 
   e = mid_chain(p, U, nullptr, B, bp, false, false, st, nullptr, 0, nullptr, disp);
   if (e != hipSuccess) return hip_fail(p, e, "forward: mid-chain");
   // part[split][l][o][n] = sum_{g in split} Fs[l][o][g] V[g][l][b]
-  const int cf = p->tune.gemm32_cfg_k < 0 && cgemm32_few_rows(g.nobs) ? kCFewRows
-                                                                          : b32_cfg(p->tune.gemm32_cfg_k, g.nobs, B);
   const int sf = b32_splits(p->tune.gemm32_splits, f.splits_f_max, g.M, g.nobs, B,
                             b32_split_cfg(p->tune.gemm32_cfg_k, B, true));
+  const int cf = p->tune.gemm32_cfg_k < 0 && cgemm32_few_rows(g.nobs)
+                     ? kCFewRows
+                     : b32_cfg(p, p->tune.gemm32_cfg_k, g.nobs, B, sf);
   const int64_t prow = 2 * (int64_t)bp;
   e = launch_cgemm32(cf, false, Fs, f.ngk, 1, (int64_t)f.nok * f.ngk, g.nobs, f.nok, f.ngk, f.ngk, U,
                      (int64_t)g.M * bp, bp, g.ngrid, B, bp, part, prow, (int64_t)f.nok * prow,
@@ -944,7 +947,7 @@ static s2w_status adjoint_b32(s2w_plan* p, const float* r, int32_t B, float* gs,
   hipError_t e = rfft_batch(r, B, g.nobs, f.nok, R, bp, g, st);
   if (e != hipSuccess) return hip_fail(p, e, "adjoint: residual transform");
   // W[g][l][b] = sum_o conj(Fs[l][o][g]) R[l][o][b]
-  const int c1 = b32_cfg(p->tune.gemm32_cfg, g.ngrid, B);
+  const int c1 = b32_cfg(p, p->tune.gemm32_cfg, g.ngrid, B, 1);
   e = launch_cgemm32(c1, true, Fs, 1, f.ngk, (int64_t)f.nok * f.ngk, g.ngrid, f.ngk, f.nok, f.nok, R, bp,
                      (int64_t)f.nok * bp, f.nok, B, bp, (float*)W, 2 * (int64_t)g.M * bp, 2 * (int64_t)bp, 0, g.M, 1,
                      st);
@@ -952,9 +955,9 @@ static s2w_status adjoint_b32(s2w_plan* p, const float* r, int32_t B, float* gs,
   e = mid_chain(p, W, nullptr, B, bp, true, false, st, nullptr, 0, nullptr, nullptr);
   if (e != hipSuccess) return hip_fail(p, e, "adjoint: mid-chain");
   // part[split][l][j][n] = sum_{g in split} conj(Gs[g][l][j]) W'[g][l][b]
-  const int c3 = b32_cfg(p->tune.adj32_cfg, g.nsub, B);
   const int sa = b32_splits(p->tune.adj32_splits, f.splits_a_max, g.M, g.nsub, B,
                             b32_split_cfg(p->tune.adj32_cfg, B, false));
+  const int c3 = b32_cfg(p, p->tune.adj32_cfg, g.nsub, B, sa);
   const int64_t prow = 2 * (int64_t)bp;
   e = mark(p->ev_begin, st);
   if (e == hipSuccess)
@@ -1539,7 +1542,7 @@ s2w_status s2w_bltt_apply(s2w_bltt* p, const float* x, int32_t B, float* y, void
   if (e != hipSuccess) return bhip(p, e, "apply: input transform");
   // part[split][l][r][n] = sum_{c in split} Fs[r][l][c] S[l][c][b]
   const int splits = p->splits_f;
-  const int cfg = cgemm32_pick(nrow, B);
+  const int cfg = cgemm32_pick(nrow, B, (int64_t)g.M * splits, p->ncu);
   const int64_t prow = 2 * (int64_t)bp;
   e = launch_cgemm32(cfg, false, Fs, (int64_t)g.M * p->ncol_k, 1, p->ncol_k, nrow, nrow, p->ncol_k, p->ncol_k,
                      S, bp, (int64_t)p->ncol_k * bp, p->ncol_k, B, bp, part, prow, (int64_t)p->nrow_k * prow,
@@ -1566,7 +1569,7 @@ s2w_status s2w_bltt_adjoint(s2w_bltt* p, const float* y, int32_t B, float* x, vo
   if (e != hipSuccess) return bhip(p, e, "adjoint: input transform");
   // part[split][l][c][n] = sum_{r in split} conj(Fs[r][l][c]) R[l][r][b]
   const int splits = p->splits_a;
-  const int cfg = cgemm32_pick(ncol, B);
+  const int cfg = cgemm32_pick(ncol, B, (int64_t)g.M * splits, p->ncu);
   const int64_t prow = 2 * (int64_t)bp;
   e = launch_cgemm32(cfg, true, Fs, 1, (int64_t)g.M * p->ncol_k, p->ncol_k, ncol, p->ncol_k, nrow, p->nrow_k, R,
                      bp, (int64_t)p->nrow_k * bp, p->nrow_k, B, bp, part, prow, (int64_t)p->ncol_k * prow,

@@ -197,7 +197,8 @@ hipError_t launch_gemm_t(int ht, int hterms, int shape, const uint32_t* Aq, int6
 //   K split over `splits` ranges (one partial per split).
 int cgemm32_rows(int cfg);
 int cgemm32_ruptures(int cfg);
-int cgemm32_pick(int nrows, int B);  // tile for a product of nrows rows and B ruptures
+// Tile for a product of nrows rows and B ruptures, launched per_tile (slots x ranges) times.
+int cgemm32_pick(int nrows, int B, int64_t per_tile, int ncu);
 constexpr int kCFewRows = 100;       // cfg of the register kernel for few rows (not transposed)
 bool cgemm32_few_rows(int nrows);
 hipError_t launch_cgemm32(int cfg, bool trans, const float2* A, int64_t a_row, int64_t a_k,

@@ -388,16 +388,22 @@ int cgemm32_ruptures(int cfg) { return kCTiles[cfg].rupts; }
 // 40 11.8 / 12.5 -> 8.2 / 7.9, 48 11.8 / 12.5 -> 8.8 / 8.8, 56 12.0 / 12.6 -> 10.2 / 10.7, 64 11.8 / 12.6 ->
 // 10.9 / 11.4.  64 observers (the whole call with 16 subfaults): B = 8 0.88 -> 0.74, 16 1.19 -> 0.78, 24
 // 1.38 -> 0.99, 32 1.39 -> 1.06, 48 1.74 -> 1.54.
-int cgemm32_pick(int nrows, int B) {
+// Workgroups share a CU's rate, so a product costs whole rounds of one per CU: with few slots or rows the tall
+// tiles leave most of them idle (whole call, B = 64, tall and now: 900 x 1,000 rows x 16 slots, 64 workgroups, 284
+// -> 118 us; 900 x 2,346 x 32, 320 workgroups, 568 -> 418).
+int cgemm32_pick(int nrows, int B, int64_t per_tile, int ncu) {
   const int nct = (B + 63) / 64, w = ((B + nct - 1) / nct + 7) / 8;  // w: units of 8 ruptures
-  auto up = [](int v, int m) { return (v + m - 1) / m * m; };
   static const int tall[] = {2, 9, 10, 11, 12, 13, 14, 15}, low[] = {4, 5, 6, 7, 8, 8, 3, 3};
-  const int lc = low[w - 1], tc = tall[w - 1];
-  // padded rows x columns over the rates of wide batches (128 x 32 between the two: 120 rows, B = 200 8.3 -> 7.3)
-  const double ct = (double)up(nrows, 256) * nct * cgemm32_ruptures(tc);
-  const double cl = 1.15 * up(nrows, 64) * nct * cgemm32_ruptures(lc);
-  const double cm = 1.07 * up(nrows, 128) * up(B, 32);
-  return cm < cl && cm < ct ? 1 : (cl < ct ? lc : tc);
+  // padded rows x columns over the rate of wide batches (128 x 32 between the two: 120 rows, B = 200 8.3 -> 7.3), in
+  // whole rounds of one workgroup per CU
+  auto cost = [&](int cfg, double slower) {
+    const int64_t rt = (nrows + cgemm32_rows(cfg) - 1) / cgemm32_rows(cfg);
+    const int64_t ct = (B + cgemm32_ruptures(cfg) - 1) / cgemm32_ruptures(cfg);
+    const int64_t rounds = (rt * ct * per_tile + ncu - 1) / ncu;
+    return slower * rounds * cgemm32_rows(cfg) * cgemm32_ruptures(cfg);
+  };
+  const double ct = cost(tall[w - 1], 1.0), cl = cost(low[w - 1], 1.15), cm = cost(1, 1.07);
+  return cm < cl && cm < ct ? 1 : (cl < ct ? low[w - 1] : tall[w - 1]);
 }
 
 // The register kernel up to two fragments of rows: whole calls of 16 subfaults x 4,000 x 256, 16 / 32 / 48
