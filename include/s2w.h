@@ -214,7 +214,8 @@ typedef struct s2w_tuning {
   int32_t adj_splits;        /* grid-row contractions: row ranges, -1 automatic (by size), 1..64 */
   int32_t batch_path_min_b;  /* reserved: ignored (the layout, fixed at plan creation, picks the path) */
   int32_t gemm_cfg;          /* batched elastic GEMM tile, 256 grid rows tall, persistent workgroups:
-                                -1 automatic (up to B = 32 the operator streams through registers, no
+                                -1 automatic (up to B = 32, unless slots and rows give few workgroups, the
+                                operator streams through registers, no
                                 tile; then 12 for B <= 64, else 18; with float16 products on
                                 bfloat16 words 16 and 24); 4 = 16 columns (four waves,
                                 register operands); 10 = 256 columns (eight waves, three-stage LDS copy

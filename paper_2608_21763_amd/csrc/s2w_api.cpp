@@ -803,7 +803,7 @@ static s2w_status forward_half(s2w_plan* p, const float* s, int32_t B, float* y,
   // up to 32 ruptures (24 with two activation terms) the operator streams through registers instead, and up
   // to 16, unless the mid-chain packs or captures, the field goes through the workspace as [l][g][b]: the 64-byte
   // runs of 8 ruptures in [g][l][b] cost the elastic product 0.7 of 3.4 ms (963 x 18,880 x 256 steps, bf16)
-  const bool stream_g = cfg < 0 && gemm_gs_fits(h.hterms_g, B);
+  const bool stream_g = cfg < 0 && gemm_gs_pays(h.hterms_g, B, g.ngrid, g.M, h.nks, p->ncu);
   if (cfg < 0) cfg = h.kt_g == 3 ? (B <= 64 ? 16 : 24) : (B <= 64 ? 12 : 18);
   // acoustic GEMM: fgemm_lds 2 takes the eight-wave kernel on full activation fragments, 3 the
   // eight-wave kernel on real-column fragments (with either the mid-chain leaves complex64),

@@ -127,6 +127,7 @@ hipError_t launch_gemm_g(int ht, int hterms, int cfg, const uint4* Gq, const flo
 // bits): elastic from k_prep_act's fragments where gemm_gs_fits (B <= 32, with two terms B <= 24) into
 // U + g*u_g + l*u_l + b, acoustic with float16 products (ht 2 or 3, up given, B <= 16) from V[l][g][b].
 bool gemm_gs_fits(int hterms, int B);
+bool gemm_gs_pays(int hterms, int B, int ngrid, int M, int nks, int ncu);  // it fits and is the faster one
 hipError_t launch_gemm_gs(int ht, int hterms, const uint4* Gq, const float* sG, const uint4* Bop, const float* sig_down,
                           float2* U, int64_t u_g, int64_t u_l, int ngrid, int M, int nks, int B, int bp, int ncu,
                           hipStream_t st);

@@ -148,14 +148,26 @@ __global__ __launch_bounds__(512) void k_gemm_gs(const uint4* __restrict__ Gq, c
 
 bool gemm_gs_fits(int hterms, int B) { return hterms * ((2 * B + 15) / 16) <= 6 && B <= 32; }
 
+// One workgroup of eight wavefronts per CU, one round: two and four rounds of smaller workgroups
+// (bursts less in step) took 3.07 and 3.17 where this takes 2.98 ms.
+static int gs_splits(int ngrid, int M, int ncu) {
+  const int nu = (ngrid + 63) / 64, ng8 = M / 8;
+  return std::max(1, std::min((ncu + ng8 - 1) / ng8, nu));
+}
+
+// Not where slots and rows give eight workgroups or fewer and each has a long chain of products (K steps x columns
+// x terms): the tiles share a slot's out over more (whole call, 900 subfaults x 64 rows, bfloat16 products, 16 and 64
+// slots: 24 ruptures 111 and 142 us streamed, 82 and 110 in tiles; 8 ruptures 64 and 98, 78 and 102).
+bool gemm_gs_pays(int hterms, int B, int ngrid, int M, int nks, int ncu) {
+  return gemm_gs_fits(hterms, B) &&
+         (M / 8 * gs_splits(ngrid, M, ncu) > 8 || nks * ((2 * B + 15) / 16) * hterms <= 200);
+}
+
 template <int HT, int H>
 static hipError_t gemm_gs_h(const uint4* Gq, const float* sG, const uint4* Bop, const float* sig_down, float2* U,
                             int64_t u_g, int64_t u_l, int ngrid, int M, int nks, int ncb, int B, int bp, int ncu,
                             hipStream_t st) {
-  // one workgroup of eight wavefronts per CU, one round: two and four rounds of smaller workgroups
-  // (bursts less in step) took 3.07 and 3.17 where this takes 2.98 ms
-  const int nu = (ngrid + 63) / 64, ng8 = M / 8;
-  const int splits = std::max(1, std::min((ncu + ng8 - 1) / ng8, nu));
+  const int ng8 = M / 8, splits = gs_splits(ngrid, M, ncu);
   const dim3 grid((unsigned)(ng8 * splits));
 #define S2W_GS(NF_)                                                                                                  \
   hipLaunchKernelGGL((k_gemm_gs<HT, H, NF_>), grid, dim3(512), 0, st, Gq, sG, Bop, sig_down, U, u_g, u_l, ngrid, \
