@@ -94,9 +94,8 @@ __global__ __launch_bounds__(256, 2) void k_bltt_gemv_row(const float4* __restri
                                                           float2* __restrict__ yh, int nrow, int M, int nc4, int cw,
                                                           int B, int nsplit) {
   __shared__ float2 res[NB][kGvRows];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // row addresses are scalar
   const int l = blockIdx.x % M, split = blockIdx.x / M;
-  const int r0 = (int)((int64_t)nrow * split / nsplit), r1 = (int)((int64_t)nrow * (split + 1) / nsplit);
   gv_f4 xr[NB][NI];  // inputs of the column chunk, zeros past B and its end
   auto inputs = [&](int c0, int n) {
 #pragma unroll
@@ -108,6 +107,8 @@ __global__ __launch_bounds__(256, 2) void k_bltt_gemv_row(const float4* __restri
         if (b < B && i < n) xr[b][t] = reinterpret_cast<const gv_f4*>(X)[((int64_t)b * M + l) * nc4 + c0 + i];
       }
   };
+  if (WHOLE) inputs(0, nc4);  // in flight under the divisions
+  const int r0 = (int)((int64_t)nrow * split / nsplit), r1 = (int)((int64_t)nrow * (split + 1) / nsplit);
   // loads past the range repeat its last row, loads past the chunk its last value (times zero inputs)
   auto load = [&](int r, int c0, int n, gv_f4 (&q)[NI]) {
     const gv_f4* a = reinterpret_cast<const gv_f4*>(K + ((int64_t)min(r, r1 - 1) * M + l) * nc4 + c0);
@@ -135,25 +136,26 @@ __global__ __launch_bounds__(256, 2) void k_bltt_gemv_row(const float4* __restri
     gv_store<NB>(re, im, lane, B, reinterpret_cast<float*>(&res[0][r - rc]), 2 * kGvRows, first);
   };
   static_assert(kGvRows % 8 == 0, "a chunk is whole turns of the loop");
-  if (r0 >= r1) return;
   gv_f4 q0[NI], q1[NI];
-  if (WHOLE) {
-    inputs(0, nc4);
-    load(r0 + wave, 0, nc4, q0);
-  }
+  auto rows = [&](int rc, int re1, int c0, int n, bool first) {  // q0 holds this wavefront's first row
+    for (int r = rc + wave; r - wave < re1; r += 8) {
+      load(r + 4, c0, n, q1);
+      sums(rc, r, first, q0);
+      load(r + 8, c0, n, q0);
+      sums(rc, r + 4, first, q1);
+    }
+  };
+  if (WHOLE && r0 < r1) load(r0 + wave, 0, nc4, q0);
   for (int rc = r0; rc < r1; rc += kGvRows) {
     const int re1 = min(rc + kGvRows, r1);
-    for (int c0 = 0; c0 < nc4; c0 += WHOLE ? nc4 : cw) {
-      const int n = WHOLE ? nc4 : min(cw, nc4 - c0);
-      if (!WHOLE) {
+    if (WHOLE) {
+      rows(rc, re1, 0, nc4, true);
+    } else {
+      for (int c0 = 0; c0 < nc4; c0 += cw) {
+        const int n = min(cw, nc4 - c0);
         inputs(c0, n);
         load(rc + wave, c0, n, q0);
-      }
-      for (int r = rc + wave; r - wave < re1; r += 8) {
-        load(r + 4, c0, n, q1);
-        sums(rc, r, WHOLE || c0 == 0, q0);
-        load(r + 8, c0, n, q0);
-        sums(rc, r + 4, WHOLE || c0 == 0, q1);
+        rows(rc, re1, c0, n, c0 == 0);
       }
     }
     gv_flush<NB>(res, B, yh, nrow, M, l, rc, re1 - rc);
