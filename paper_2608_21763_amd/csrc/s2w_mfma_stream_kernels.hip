@@ -24,7 +24,7 @@ namespace s2w {
 // in groups of GRP K steps, the next group (of the same or the next unit) loaded under the products
 // of the current one.  The eight wavefronts of a workgroup take eight consecutive slots of the same rows.
 //
-// Bound by HBM, and by its dislike of mixed traffic: a read stream of 18.6 GB at 7.0 TB/s falls to 5.3
+// Bound by HBM, and by its dislike of mixed traffic: a read stream of 18.9 GB at 6.7 to 7.0 TB/s falls to 5.2
 // TB/s when 1 KB is written after every 61 KB read (1.6 % of the traffic), and comes back to 6.5 TB/s when
 // the same bytes leave in bursts of 128 KB per CU with non-temporal stores.  So the products of NU units
 // collect in 128 KB of LDS and leave together.  963 x 18,880 x 256 slots, bf16, 8 ruptures (18.6 GB):
